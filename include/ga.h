@@ -251,9 +251,12 @@ void ga_destroy(ga_run* run);
  * (Sec. 2 Methods). The torus is cut into tiles of tile_w x tile_h islands
  * (the last column and row of tiles ragged); one workgroup per tile runs every
  * generation of a launch, all tiles' workgroups resident at once. Between
- * generations tiles exchange only their edge islands' emissions through the
- * HBM outbox, each tile waiting (a bounded number of times) until its four
- * neighbouring tiles have published generation t - 1. HBM carries the
+ * generations tiles exchange only their edge islands' emissions through a
+ * small area in HBM (64 bytes per island, 128 with a genome string; allocated
+ * by ga_init for a run that could take this form and released by ga_destroy;
+ * without it, when no memory is left, a launch of several tiles runs one
+ * generation), an island waiting (a bounded number of times) until its
+ * neighbours in other tiles have sent their emissions of t - 1. HBM carries the
  * population only at the start and end of a launch (at most 2^16 generations
  * or about 2^34 agent-generations each). Needs a tiling whose tiles fit the
  * LDS of a CU (160 KiB: per agent 4 bytes each of fitness, T, the surface

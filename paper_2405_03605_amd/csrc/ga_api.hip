@@ -465,13 +465,16 @@ int check_tile_waits(ga_run* r) {
 int step_tiles(ga_run* r, uint64_t n) {
   const ga::RunView& v = r->view;
   const uint32_t n_tiles = v.tiles_x * v.tiles_y;
-  // about 2^34 agent-generations, at most 2^16 generations, per launch
+  // about 2^34 agent-generations, at most 2^16 generations, per launch; one
+  // generation if the exchange area could not be allocated
+  const bool alone = n_tiles > 1 && v.migration && !v.exchange;
   const uint64_t slice_max =
-      std::max<uint64_t>(1, std::min<uint64_t>(1u << 16, (1ull << 34) / std::max(1u, v.agents)));
+      alone ? 1
+            : std::max<uint64_t>(1, std::min<uint64_t>(1u << 16,
+                                                       (1ull << 34) / std::max(1u, v.agents)));
   uint64_t left = n;
   while (left > 0) {
     const uint64_t slice = std::min(left, slice_max);
-    GA_HIP(ga::launch_fill(v.prog, (uint32_t)r->gen_host, n_tiles, r->stream), "progress reset");
     GA_HIP(ga::launch_tiles(v, slice, r->stream), "tile launch");
     GA_HIP(ga::launch_advance(v.gen, slice, r->stream), "advance launch");
     left -= slice;
@@ -612,7 +615,44 @@ size_t ga_state_bytes(const ga_config* cfg) {
   return layout_of(cfg).total;
 }
 
-int ga_init(const ga_config* cfg, void* dev_mem, size_t bytes, void* hip_stream, ga_run** out) {
+}  // extern "C"
+
+namespace {
+
+// The exchange area of the LDS-resident form: the library's own small
+// allocation for a run that may be stepped by itself and whose population could
+// fit the GPU's LDS. Without it (no memory left) the form runs one
+// generation per launch. Allocated here, not on the first step, so that a step
+// can be captured.
+void alloc_exchange(ga_run* r) {
+  ga::RunView& v = r->view;
+  int device = 0, cus = 0;
+  if (hipGetDevice(&device) != hipSuccess ||
+      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess)
+    return;
+  const bool strings = ga::model_has_string_host(v.model);
+  const size_t agent_bytes = 4 * (size_t)(2 + v.words + (strings ? 2 : 0));
+  if (v.agents * agent_bytes > (size_t)cus * kMaxGroupLds) return;
+  const size_t bytes = 2 * (size_t)v.islands * ga::exchange_words(strings) * 8;
+  void* p = nullptr;
+  if (hipMalloc(&p, bytes) != hipSuccess) {
+    (void)hipGetLastError();
+    return;
+  }
+  v.exchange = static_cast<unsigned long long*>(p);
+}
+
+// Empty the exchange area of a run at generation t.
+hipError_t clear_exchange(const ga::RunView& v, uint64_t t, hipStream_t s) {
+  if (!v.exchange) return hipSuccess;
+  const size_t words =
+      2 * (size_t)v.islands * ga::exchange_words(ga::model_has_string_host(v.model)) * 2;
+  return ga::launch_fill(reinterpret_cast<uint32_t*>(v.exchange), ga::exchange_empty(t), words, s);
+}
+
+// ga_init; `alone` for a run that may be stepped by itself (not a pool's).
+int init_run(const ga_config* cfg, void* dev_mem, size_t bytes, void* hip_stream, bool alone,
+             ga_run** out) {
   std::string why;
   if (!out) return fail(GA_EINVAL, "out is NULL");
   *out = nullptr;
@@ -674,12 +714,28 @@ int ga_init(const ga_config* cfg, void* dev_mem, size_t bytes, void* hip_stream,
   // outbox headers, generation 0.
   hipError_t e = ga::launch_fill(reinterpret_cast<uint32_t*>(b), 0u, lay.total / 4, r->stream);
   if (e == hipSuccess) e = ga::launch_init(v, r->stream);
+  if (e == hipSuccess && alone && !async && v.migration) {
+    alloc_exchange(r);
+    e = clear_exchange(v, 0, r->stream);
+  }
   if (e != hipSuccess) {
+    if (v.exchange) {
+      (void)hipStreamSynchronize(r->stream);
+      (void)hipFree(v.exchange);
+    }
     delete r;
     return hip_fail(e, "init fill");
   }
   *out = r;
   return GA_OK;
+}
+
+}  // namespace
+
+extern "C" {
+
+int ga_init(const ga_config* cfg, void* dev_mem, size_t bytes, void* hip_stream, ga_run** out) {
+  return init_run(cfg, dev_mem, bytes, hip_stream, true, out);
 }
 
 uint64_t ga_generation(const ga_run* r) { return r ? r->gen_host : 0; }
@@ -935,6 +991,7 @@ int ga_write_population(ga_run* r, const float* fitness, const uint32_t* T,
     GA_HIP(hipMemcpyAsync(v.ob[p_new], v.ob[p_old], (size_t)v.island_stride * st * 4, d2d, s),
            "move outbox");
   }
+  GA_HIP(clear_exchange(v, generation, s), "reset exchange");
   unsigned long long t = generation;
   GA_HIP(hipMemcpyAsync(v.gen, &t, sizeof(t), h2d, s), "write generation");
   GA_HIP(hipStreamSynchronize(s), "stream sync");
@@ -1026,6 +1083,7 @@ void ga_destroy(ga_run* r) {
   (void)hipStreamSynchronize(r->stream);
   drop_graph(r);
   if (r->capture_stream) (void)hipStreamDestroy(r->capture_stream);
+  if (r->view.exchange) (void)hipFree(r->view.exchange);
   delete r;
 }
 
@@ -1523,7 +1581,7 @@ int ga_pool_admit(ga_pool* p, const ga_config* cfg, uint64_t n_gens, uint64_t* t
   const size_t off = pool_take(p, need);
   if (off == SIZE_MAX) return fail(GA_ENOMEM, "no free block holds the run");
   ga_run* r = nullptr;
-  int rc = ga_init(cfg, p->base + off, need, p->batch->stream, &r);
+  int rc = init_run(cfg, p->base + off, need, p->batch->stream, false, &r);
   if (rc == GA_OK) {
     rc = ga_batch_add(p->batch, r, n_gens);
     if (rc != GA_OK) ga_destroy(r);

@@ -13,6 +13,8 @@ namespace ga {
 
 constexpr uint32_t kMulA = 0xD2511F53u;   // Philox4x32 round multipliers
 constexpr uint32_t kMulB = 0xCD9E8D57u;
+constexpr uint32_t kMulAInverse = 0x991A7CDBu;  // kMulA * kMulAInverse = 1 mod 2^32
+static_assert(kMulA * kMulAInverse == 1u, "inverse of the first multiplier");
 constexpr uint32_t kWeylA = 0x9E3779B9u;  // key schedule increments
 constexpr uint32_t kWeylB = 0xBB67AE85u;
 
@@ -32,19 +34,71 @@ __device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) {
 
 __device__ __forceinline__ uint32_t hi32(uint64_t v) { return (uint32_t)(v >> 32); }
 
+// A copy of a wavefront-uniform value in a vector register.
+__device__ __forceinline__ uint32_t in_vgpr(uint32_t x) {
+  uint32_t r;
+  asm("v_mov_b32 %0, %1" : "=v"(r) : "s"(x));
+  return r;
+}
+
+// The value as it is, but opaque to the optimizer: an XOR of invariants stays
+// one invariant instead of being split back over a loop's own operands.
+__device__ __forceinline__ uint32_t whole(uint32_t x) {
+  asm("" : "+v"(x));
+  return x;
+}
+
+// (a & b) | c in one three-input bitwise op. On gfx950 the bitwise, add and
+// immediate-shift ops issue in about 3 cycles a wavefront while no operand is
+// a scalar register, against 4.7 with one, and 4.9 for v_and_or, v_bfi and
+// shifts by a register whatever their operands (eight wavefronts per SIMD,
+// nominal 2.4 GHz): the hot loops keep their constants in vector registers.
+__device__ __forceinline__ uint32_t and_or(uint32_t a, uint32_t b, uint32_t c) {
+  return __builtin_amdgcn_bitop3_b32(a, b, c, 0xEA);
+}
+
+// The key of Philox round r: the run's key plus r Weyl increments. HELD keeps
+// the keys of rounds 3..9 in vector registers for a kernel's lifetime (14
+// registers; a round's two XORs then issue in 3 cycles each instead of 4.7);
+// otherwise they are scalar sums.
+template <bool HELD>
+struct RoundKeys;
+
+template <>
+struct RoundKeys<false> {
+  uint32_t k0, k1;
+  __device__ __forceinline__ RoundKeys(uint32_t key0, uint32_t key1) : k0(key0), k1(key1) {}
+  __device__ __forceinline__ uint32_t a(int r) const { return k0 + (uint32_t)r * kWeylA; }
+  __device__ __forceinline__ uint32_t b(int r) const { return k1 + (uint32_t)r * kWeylB; }
+};
+
+template <>
+struct RoundKeys<true> {
+  uint32_t ka[7], kb[7];
+  __device__ __forceinline__ RoundKeys(uint32_t key0, uint32_t key1) {
+#pragma unroll
+    for (int r = 0; r < 7; ++r) {
+      ka[r] = in_vgpr(key0 + (uint32_t)(r + 3) * kWeylA);
+      kb[r] = in_vgpr(key1 + (uint32_t)(r + 3) * kWeylB);
+    }
+  }
+  __device__ __forceinline__ uint32_t a(int r) const { return ka[r - 3]; }
+  __device__ __forceinline__ uint32_t b(int r) const { return kb[r - 3]; }
+};
+
 // Philox4x32-10 (Salmon, Moraes, Dror, Shaw, SC'11), rounds FIRST..9 applied
-// to counter state (c0..c3) with the round-0 key (k0, k1): each round takes both
-// halves of two 32x32->64 products and mixes the high halves with the other
-// two words and the round key (k + round * Weyl increment).
-template <int FIRST>
+// to counter state (c0..c3): each round takes both halves of two 32x32->64
+// products and mixes the high halves with the other two words and the round's
+// key.
+template <int FIRST, bool HELD>
 __device__ __forceinline__ Block philox_rounds(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3,
-                                               uint32_t k0, uint32_t k1) {
+                                               const RoundKeys<HELD>& key) {
 #pragma unroll
   for (int round = FIRST; round < 10; ++round) {
     const uint64_t pa = (uint64_t)kMulA * c0;
     const uint64_t pb = (uint64_t)kMulB * c2;
-    const uint32_t n0 = xor3(hi32(pb), c1, k0 + (uint32_t)round * kWeylA);
-    const uint32_t n2 = xor3(hi32(pa), c3, k1 + (uint32_t)round * kWeylB);
+    const uint32_t n0 = xor3(hi32(pb), c1, key.a(round));
+    const uint32_t n2 = xor3(hi32(pa), c3, key.b(round));
     c1 = (uint32_t)pb;
     c3 = (uint32_t)pa;
     c0 = n0;
@@ -55,26 +109,23 @@ __device__ __forceinline__ Block philox_rounds(uint32_t c0, uint32_t c1, uint32_
 
 __device__ __forceinline__ Block philox10(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3,
                                           uint32_t k0, uint32_t k1) {
-  return philox_rounds<0>(c0, c1, c2, c3, k0, k1);
+  return philox_rounds<0, false>(c0, c1, c2, c3, RoundKeys<false>(k0, k1));
 }
 
-// Per-child stream blocks for one lane across a chunk. The counter is
-// (slot, island, t_lo, t_hi*4 + stream): only the island word changes between a lane's
-// iterations, so everything of rounds 0-2 that does not depend on it is
-// computed once. The remaining per-block cost is 2 + 7*2 products and 3 + 7*2
-// three-input ops.
+// Stream blocks for one lane across many islands. The counter is (slot,
+// island, t_lo, t_hi*4 + stream): only the island word changes between a
+// lane's blocks, so everything of rounds 0-2 that does not depend on it is
+// computed once. The remaining per-block cost is 2 + 7*2 products and 4 + 7*2
+// XORs.
 struct SelectStream {
   uint32_t x0;      // round 0: c0' = x0 ^ island
   uint32_t inv_a;   // round 1: c2'' = hi(M0*c0') ^ inv_a
   uint32_t inv_b;   // round 2: c0''' = hi(M1*c2'') ^ inv_b
   uint32_t inv_c;   // round 2: c2''' = inv_c ^ lo(M0*c0')
   uint32_t inv_d;   // round 2: c3''' = inv_d
-  uint32_t k0, k1;
 
   __device__ __forceinline__ void init(uint32_t slot, uint32_t t_lo, uint32_t t_hi4, uint32_t key0,
                                        uint32_t key1, uint32_t stream) {
-    k0 = key0;
-    k1 = key1;
     // round 0 on (slot, island, t_lo, t_hi4)
     const uint64_t pa0 = (uint64_t)kMulA * slot;
     const uint64_t pb0 = (uint64_t)kMulB * t_lo;
@@ -94,16 +145,38 @@ struct SelectStream {
     inv_d = (uint32_t)pa2;                       // c3_3
   }
 
-  __device__ __forceinline__ Block block(uint32_t island) const {
-    const uint32_t c0_1 = x0 ^ island;
-    const uint64_t pa1 = (uint64_t)kMulA * c0_1;
+  // The invariants as single vector registers (see whole).
+  __device__ __forceinline__ void hold() {
+    x0 = whole(x0);
+    inv_a = whole(inv_a);
+    inv_b = whole(inv_b);
+    inv_c = whole(inv_c);
+    inv_d = whole(inv_d);
+  }
+
+  // Round 1's product of the island word: the same for every slot and stream
+  // of an island in a generation (and the island back from it: the multiplier
+  // is odd, so its low word determines the counter word).
+  __device__ __forceinline__ uint64_t of_island(uint32_t island) const {
+    return (uint64_t)kMulA * (x0 ^ island);
+  }
+  __device__ __forceinline__ uint32_t island_of(uint64_t pa1) const {
+    return ((uint32_t)pa1 * kMulAInverse) ^ x0;
+  }
+
+  template <bool HELD>
+  __device__ __forceinline__ Block block(uint32_t island, const RoundKeys<HELD>& key) const {
+    return block_from(of_island(island), key);
+  }
+  template <bool HELD>
+  __device__ __forceinline__ Block block_from(uint64_t pa1, const RoundKeys<HELD>& key) const {
     const uint32_t c2_2 = hi32(pa1) ^ inv_a;
     const uint32_t c3_2 = (uint32_t)pa1;
     const uint64_t pb2 = (uint64_t)kMulB * c2_2;
     const uint32_t c0_3 = hi32(pb2) ^ inv_b;
     const uint32_t c1_3 = (uint32_t)pb2;
     const uint32_t c2_3 = inv_c ^ c3_2;
-    return philox_rounds<3>(c0_3, c1_3, c2_3, inv_d, k0, k1);
+    return philox_rounds<3, HELD>(c0_3, c1_3, c2_3, inv_d, key);
   }
 };
 
@@ -118,10 +191,13 @@ struct Genome {
 // What a model's mutate may use beyond the child's selection-stream block:
 // the mutation probability (and the treatment law's thresholds) and, for
 // draws of its own, the lane's mutation stream at the child's island.
+template <bool HELD>
 struct MutateArgs {
   uint32_t p32, law, p_ben, p_any;
   const SelectStream* mut;
-  uint32_t island;
+  const RoundKeys<HELD>* key;
+  uint64_t island;  // the island's product (SelectStream::of_island)
+  __device__ __forceinline__ Block draw() const { return mut->block_from(island, *key); }
 };
 
 }  // namespace ga
@@ -136,7 +212,7 @@ namespace ga {
 // which left the retained set when epoch e began. Written ranks have the form
 // odd << shift, so the walk only renormalises the odd part until the rank
 // falls below S.
-static __device__ __noinline__ uint32_t surface_site_walk(uint32_t r, uint32_t e, uint32_t s) {
+__device__ __forceinline__ uint32_t surface_site_walk(uint32_t r, uint32_t e, uint32_t s) {
   const uint32_t half = 1u << (s - 1u);
   uint32_t odd = (((r >> e) - half) << 1) | 1u;
   uint32_t shift = e - 1u;
@@ -227,12 +303,14 @@ __device__ __forceinline__ uint32_t xcd_band(uint32_t g, uint32_t n) {
 __device__ __forceinline__ uint32_t xcd_band_group() { return xcd_band(blockIdx.x, gridDim.x); }
 
 // Per-lane constants of one generation's children: the lane's slot in its
-// island, the permute address of slot 0 of that island, and the selection
-// (and, under the treatment law, mutation) stream with everything hoisted
-// that depends only on the slot and the generation.
+// island, the address its island's members are found at (see the parent
+// accessors below), and the selection (and, under the treatment law, mutation)
+// stream with everything hoisted that depends only on the slot and the
+// generation.
 struct BreedLane {
   uint32_t slot;
-  uint32_t lane0_addr;
+  uint32_t base;       // address of the island's slot 0
+  uint32_t slot_mask;  // (N - 1) * 4: a draw's bits that pick a slot, in place
   uint32_t t_lo, t_hi4;
   SelectStream sel, mut;
   // the mutation thresholds, compared lane by lane: held in vector registers
@@ -240,20 +318,14 @@ struct BreedLane {
   uint32_t p32, p_ben, p_any;
 };
 
-// A copy of a wavefront-uniform value in a vector register.
-__device__ __forceinline__ uint32_t in_vgpr(uint32_t x) {
-  uint32_t r;
-  asm("v_mov_b32 %0, %1" : "=v"(r) : "s"(x));
-  return r;
-}
-
 template <int LC>
 __device__ __forceinline__ BreedLane breed_lane(const RunView& v, uint64_t t) {
   const uint32_t L = LC >= 0 ? (uint32_t)LC : v.log2n;
   const uint32_t lane = __lane_id();
   BreedLane b;
   b.slot = lane & ((1u << L) - 1u);
-  b.lane0_addr = (lane & ~((1u << L) - 1u)) << 2;
+  b.base = (lane & ~((1u << L) - 1u)) << 2;
+  b.slot_mask = in_vgpr(((1u << L) - 1u) << 2);
   b.t_lo = (uint32_t)t;
   b.t_hi4 = (uint32_t)(t >> 32) << 2;
   b.sel.init(b.slot, b.t_lo, b.t_hi4, v.seed, v.run_id, kStreamSelect);
@@ -264,18 +336,54 @@ __device__ __forceinline__ BreedLane breed_lane(const RunView& v, uint64_t t) {
   return b;
 }
 
+// Where a tournament finds the members of the lane's island. The address of a
+// member is its island's base | slot * 4, the slot taken from byte m of the
+// draw without leaving its place: ((word >> s) & slot_mask) | base.
+
+// Members in the registers of this wavefront's lanes (cross-lane permutes;
+// every lane must take part).
+template <int SW, bool STR>
+struct LaneParents {
+  const Genome& g;
+  __device__ __forceinline__ float fitness(uint32_t at) const { return permute(g.f, at); }
+  __device__ __forceinline__ void copy(Genome& c, uint32_t at) const {
+    c.T = permute(g.T, at);
+    c.D0 = permute(g.D0, at);
+    c.D1 = SW > 1 ? permute(g.D1, at) : 0u;
+    if (STR) {
+      c.P0 = permute(g.P0, at);
+      c.P1 = permute(g.P1, at);
+    }
+  }
+};
+
+// The steady policy's deposit of rank q on 2^s sites writes iff q has no set
+// bit below its top s bits (every rank below 2^s; after that the multiples of
+// 2^e, e = bitlen(q) - s). May: three ops, true for every rank that writes and
+// (rounded to binary32) for a few from 2^24 on that do not; writes: exact.
+__device__ __forceinline__ bool steady_may_write(uint32_t q, uint32_t s) {
+  return (__float_as_uint((float)q) & ((1u << (24u - s)) - 1u)) == 0u;
+}
+__device__ __forceinline__ bool steady_writes(uint32_t q, uint32_t s) {
+  const uint32_t len = 32u - __clz(q);
+  return len <= s || (q & ((1u << (len - s)) - 1u)) == 0u;
+}
+
 // Steps 3-7 of generation t for the child in this lane's slot of `island`
 // (paper Sec. 2): evaluation (the fitness word), a tournament of k entrants
 // drawn with replacement from the lane's island (first strict maximum in draw
-// order wins; neutral runs take entrant 0), the winner's genome copied by
-// cross-lane permutes, the model's mutation, and one stratum deposit at rank
-// T followed by T + 1. `g` is this lane's post-immigration genome; every lane
-// of the wavefront must call this together (the permutes read all lanes).
+// order wins; neutral runs take entrant 0), the winner's genome copied from
+// `parents`, the model's mutation, and one stratum deposit at rank T followed
+// by T + 1. `island` is its product in the lane's streams (of_island), `r` the
+// child's selection block.
 // LC / SWC: log2 N and surface words fixed at compile time, or -1 to read
 // them from the view.
-template <int LC, int SWC, typename Model, bool WIDE>
-__device__ __forceinline__ Genome breed(const RunView& v, const BreedLane& b, const Genome& g,
-                                        uint32_t island) {
+// PLAIN: a tournament of two under the discrete mutation law, the common run,
+// known at compile time.
+template <int LC, int SWC, typename Model, bool WIDE, bool PLAIN, bool HELD, typename Parents>
+__device__ __forceinline__ Genome breed(const RunView& v, const BreedLane& b,
+                                        const Parents& parents, const Block& r, uint64_t island,
+                                        const RoundKeys<HELD>& key) {
   const uint32_t L = LC >= 0 ? (uint32_t)LC : v.log2n;
   const uint32_t SW = SWC >= 0 ? (uint32_t)SWC : v.words;
   // surface: S = 2^s_log sites of 2^dlog-bit differentia under the steady
@@ -286,44 +394,57 @@ __device__ __forceinline__ Genome breed(const RunView& v, const BreedLane& b, co
   const bool hybrid = WIDE && v.policy == 2u;
   const uint32_t s_log = WIDE ? v.s_log : 4u + SW;
 
-  // 3-5. evaluate (read fitness) and run the tournament over permuted entrants
-  const Block r = b.sel.block(island);
-  uint32_t best = b.lane0_addr + (((r.x & 0xFFu) >> (8u - L)) << 2);
-  float fbest = permute(g.f, best);
-  // entrants 1..k-1: bytes 1..7 of (w0, w1), little-endian. Entrant 1 is
-  // taken apart (k = 2 is the common size), the rest in a uniform loop (no
-  // per-entrant condition kept live across the caller's loop).
-  const uint32_t k = v.selection ? v.k : 1u;
+  // 3-5. evaluate (read fitness) and run the tournament: entrant m takes byte
+  // m of (w0, w1), little-endian. Entrant 1 is taken apart (k = 2 is the
+  // common size); beyond it entrants go in pairs, all of a pair's members
+  // fetched before any is compared, an odd last one left out of the
+  // comparison. The conditions are uniform.
+  auto entrant = [&](uint32_t word, uint32_t byte) {
+    return and_or(word >> (8u * byte + 6u - L), b.slot_mask, b.base);
+  };
+  uint32_t best = entrant(r.x, 0);
+  float fbest = parents.fitness(best);
+  const uint32_t k = PLAIN ? 2u : v.selection ? v.k : 1u;
+  auto meet = [&](uint32_t at, float f, bool in) {
+    const bool wins = in && f > fbest;
+    best = wins ? at : best;
+    fbest = wins ? f : fbest;
+  };
   if (k > 1u) {
-    const uint32_t cand = b.lane0_addr + ((((r.x >> 8) & 0xFFu) >> (8u - L)) << 2);
-    const float fc = permute(g.f, cand);
-    if (fc > fbest) {
-      best = cand;
-      fbest = fc;
-    }
-    uint64_t rest = (((uint64_t)r.y << 32) | r.x) >> 16;
-    for (uint32_t m = 2; m < k; ++m) {
-      const uint32_t cand_m = b.lane0_addr + ((((uint32_t)rest & 0xFFu) >> (8u - L)) << 2);
-      rest >>= 8;
-      const float fm = permute(g.f, cand_m);
-      if (fm > fbest) {
-        best = cand_m;
-        fbest = fm;
+    const uint32_t a1 = entrant(r.x, 1);
+    const float f1 = parents.fitness(a1);
+    if (k > 2u) {
+      const uint32_t a2 = entrant(r.x, 2), a3 = entrant(r.x, 3);
+      const float f2 = parents.fitness(a2), f3 = parents.fitness(a3);
+      if (k > 4u) {
+        const uint32_t a4 = entrant(r.y, 0), a5 = entrant(r.y, 1);
+        const float f4 = parents.fitness(a4), f5 = parents.fitness(a5);
+        meet(a1, f1, true);
+        meet(a2, f2, true);
+        meet(a3, f3, true);
+        meet(a4, f4, true);
+        meet(a5, f5, k > 5u);
+        if (k > 6u) {
+          const uint32_t a6 = entrant(r.y, 2), a7 = entrant(r.y, 3);
+          const float f6 = parents.fitness(a6), f7 = parents.fitness(a7);
+          meet(a6, f6, true);
+          meet(a7, f7, k > 7u);
+        }
+      } else {
+        meet(a1, f1, true);
+        meet(a2, f2, true);
+        meet(a3, f3, k > 3u);
       }
+    } else {
+      meet(a1, f1, true);
     }
   }
   Genome c;
-  c.T = permute(g.T, best);
-  c.D0 = permute(g.D0, best);
-  c.D1 = SW > 1 ? permute(g.D1, best) : 0u;
-  if (Model::kString) {
-    c.P0 = permute(g.P0, best);
-    c.P1 = permute(g.P1, best);
-  }
+  parents.copy(c, best);
   c.f = fbest;
 
   // 6. mutation, by the genome model
-  MutateArgs ma{b.p32, v.law, b.p_ben, b.p_any, &b.mut, island};
+  MutateArgs<HELD> ma{b.p32, PLAIN ? 0u : v.law, b.p_ben, b.p_any, &b.mut, &key, island};
   Model::mutate(c, r, ma);
 
   // 7. stratum deposit at rank T, then T + 1. The hybrid policy sends even
@@ -337,37 +458,39 @@ __device__ __forceinline__ Genome breed(const RunView& v, const BreedLane& b, co
     on_tilted = (c.T & 1u) != 0u;
     site_base = on_tilted ? 32u : 0u;
   }
-  uint32_t site = q;
-  bool write = true;
-  if (on_tilted) {
-    // level k = trailing zeros of q (capped at 31; q = 0 counts as 31), slot
-    // (q >> (k+1)) mod m ((q >> 31) mod m on level 31), m = sites / 32
-    const uint32_t m_log = q_log - 5u;
-    const uint32_t k = q ? min((uint32_t)__ffs(q) - 1u, 31u) : 31u;
-    const uint32_t ring = (k < 31u ? q >> (k + 1u) : q >> 31) & ((1u << m_log) - 1u);
-    site = (k << m_log) + ring;
-  } else if (q >= (1u << q_log)) {
-    const uint32_t e = (32u - __clz(q)) - q_log;
-    write = (q & ((1u << e) - 1u)) == 0u;
-    if (write) site = surface_site_walk(q, e, q_log);
-  }
-  site += site_base;
-  if (write) {
+  if (on_tilted || steady_may_write(q, q_log)) {
+    uint32_t site = q;
+    bool write = true;
+    if (on_tilted) {
+      // level k = trailing zeros of q (capped at 31; q = 0 counts as 31), slot
+      // (q >> (k+1)) mod m ((q >> 31) mod m on level 31), m = sites / 32
+      const uint32_t m_log = q_log - 5u;
+      const uint32_t lev = q ? min((uint32_t)__ffs(q) - 1u, 31u) : 31u;
+      const uint32_t ring = (lev < 31u ? q >> (lev + 1u) : q >> 31) & ((1u << m_log) - 1u);
+      site = (lev << m_log) + ring;
+    } else if (q >= (1u << q_log)) {
+      write = steady_writes(q, q_log);
+      if (write) site = surface_site_walk(q, (32u - __clz(q)) - q_log, q_log);
+    }
+    site += site_base;
     // the differentia: one bit, the top bit of the selection block's w3;
     // b = 2^dlog > 1 bits, the top b bits of word 0 of a block of their own
     // (mutation stream, counter word 0 = slot + 256), drawn only by the
     // lanes that write
     const uint32_t pos = site << dlog;
-    uint32_t value = r.w >> 31;
-    if (WIDE && dlog != 0u)
-      value = philox10(b.slot + 256u, island, b.t_lo, b.t_hi4 | kStreamMutate, v.seed, v.run_id).x >>
-              (32u - (1u << dlog));
-    const uint32_t field = ((2u << ((1u << dlog) - 1u)) - 1u) << (pos & 31u);
-    const uint32_t bits = value << (pos & 31u);
+    uint32_t value = (uint32_t)((int32_t)r.w >> 31);  // the bit, in every place
+    uint32_t field = 1u << (pos & 31u);
+    if (WIDE && dlog != 0u) {
+      value = philox10(b.slot + 256u, b.sel.island_of(island), b.t_lo, b.t_hi4 | kStreamMutate,
+                       v.seed, v.run_id).x >>
+              (32u - (1u << dlog)) << (pos & 31u);
+      field = ((2u << ((1u << dlog) - 1u)) - 1u) << (pos & 31u);
+    }
+    field = write ? field : 0u;
     if (SW == 1 || pos < 32u) {
-      c.D0 = (c.D0 & ~field) | bits;
+      c.D0 = (c.D0 & ~field) | (value & field);
     } else {
-      c.D1 = (c.D1 & ~field) | bits;
+      c.D1 = (c.D1 & ~field) | (value & field);
     }
   }
   c.T += 1u;

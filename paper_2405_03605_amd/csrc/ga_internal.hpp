@@ -62,10 +62,19 @@ struct RunView {
   // policy 0 "doubling steady", 1 "tilted", 2 "hybrid"
   uint32_t s_log, dlog, policy;
   // LDS-resident tiles (synchronous schedule): tiles of tile_w x tile_h
-  // islands, tiles_x across and tiles_y down (the last ones ragged); tile c's
-  // progress word is prog[c]
+  // islands, tiles_x across and tiles_y down (the last ones ragged), and the
+  // exchange area between them: an emission of generation g by island i is in
+  // exchange[((g & 1) * islands + i) * exchange_words + k], genome word k in
+  // the low half (fitness, T, surface words, string words), above it
+  // (g << 1) | bit k of the direction (bits 0 and 1)
   uint32_t tile_w, tile_h, tiles_x, tiles_y;
+  unsigned long long* exchange;
 };
+
+// 64-bit words of an exchange slot, and what an empty slot's halves hold while
+// the run is at generation t: no generation a launch from t on waits for.
+constexpr uint32_t exchange_words(bool strings) { return strings ? 8u : 4u; }
+constexpr uint32_t exchange_empty(uint64_t t) { return ((uint32_t)t - 4u) << 1; }
 
 // Asynchronous pacing: no bound on how far an island may run ahead, and the
 // number of progress checks before an island goes on regardless.
@@ -104,8 +113,8 @@ constexpr int kMaxWavesPerGroup = 16;
 hipError_t launch_generation(const RunView& v, uint32_t gen_offset, uint32_t waves,
                              uint32_t waves_per_group, hipStream_t stream);
 // The LDS-resident tile form: one persistent launch of n_gens generations,
-// one workgroup per tile (v.tile_* set; v.prog holds a word per tile, equal to
-// the generation counter's low word before the launch).
+// one workgroup per tile (v.tile_* set; v.exchange unless there is one tile, one
+// generation or no migration).
 hipError_t launch_tiles(const RunView& v, uint64_t n_gens, hipStream_t stream);
 // LDS bytes and threads of a tile's workgroup, and how many such workgroups
 // one CU holds at once.

@@ -329,6 +329,7 @@ __device__ __forceinline__ void chunk_generation(const RunView& v, uint32_t base
 
   // ---- iterations: lanes are agent slots ------------------------------------
   const BreedLane bl = breed_lane<LC>(v, t);
+  const RoundKeys<false> key(v.seed, v.run_id);
   const uint32_t slot = bl.slot;
   const uint32_t slot_bytes = slot * 0x01010101u;
   const uint32_t emit_base = 4u * v.ipw;
@@ -380,7 +381,10 @@ __device__ __forceinline__ void chunk_generation(const RunView& v, uint32_t base
     }
 
     // 3-7. tournament, copy, mutation, deposit
-    const Genome c = breed<LC, SWC, Model, WIDE>(v, bl, cur, island);
+    const LaneParents<SWC, kStr> parents{cur};
+    const uint64_t pa = bl.sel.of_island(island);
+    const Genome c =
+        breed<LC, SWC, Model, WIDE, false>(v, bl, parents, bl.sel.block_from(pa, key), pa, key);
 
     *at_byte(pf, off) = c.f;
     *at_byte(pT, off) = c.T;

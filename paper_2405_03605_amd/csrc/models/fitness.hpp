@@ -20,18 +20,21 @@ struct FitnessModel {
   //   deleterious (-|Z|) iff p_ben <= w2 < p_any; Z is the variance-matched
   //   sum of the eight 16-bit halves of the child's mutation-stream block
   //   (Irwin-Hall n = 8), one correctly rounded product.
-  __device__ static void mutate(Genome& c, const Block& r, const MutateArgs& a) {
+  template <typename Args>
+  __device__ static void mutate(Genome& c, const Block& r, const Args& a) {
     if (a.law == 0) {
       if (r.z < a.p32) {
-        // di * 0.5 is exact, so a fused multiply-add rounds like the plain add
-        const int di = (int)__umulhi(r.w & 0x7FFFFFFFu, 10u) - 2;  // -2..2
+        // di * 0.5 is exact, so a fused multiply-add rounds like the plain add;
+        // the product's high word takes the -2 as a 64-bit addend
+        const int di =  // -2..2
+            (int)(((uint64_t)(r.w & 0x7FFFFFFFu) * 10u + 0xFFFFFFFE00000000ull) >> 32);
         c.f = __fadd_rn(c.f, (float)di * 0.5f);
       }
     } else {
       const bool ben = r.z < a.p_ben;
       const bool del = !ben && r.z < a.p_any;
       if (ben || del) {
-        const Block m = a.mut->block(a.island);
+        const Block m = a.draw();
         const uint32_t sum = (m.x & 0xFFFFu) + (m.x >> 16) + (m.y & 0xFFFFu) + (m.y >> 16) +
                              (m.z & 0xFFFFu) + (m.z >> 16) + (m.w & 0xFFFFu) + (m.w >> 16);
         const float size = fabsf(__fmul_rn((float)((int)sum - 262140), 0x1.3988e2p-16f));

@@ -3,7 +3,7 @@
 // a type with
 //   static constexpr bool kString;   // carries the 64-bit string P0, P1
 //   static void initialize(Genome&, const Block& draw);  // founders
-//   static void mutate(Genome& child, const Block& r, const MutateArgs&);
+//   static void mutate(Genome& child, const Block& r, const Args&);  // a MutateArgs
 //   static float evaluate(const Genome&);
 // and is compiled into every generation kernel as a template argument, so
 // each model gets specialised code. Adding one: its header below and one

@@ -24,7 +24,8 @@ struct StringModel {
   // with the same probability p as the fitness-valued genome (word 2 of the
   // selection block below p32), flip bit (w3 mod 64): the bits the fitness
   // delta would use, disjoint from the differentia bit (w3's top bit)
-  __device__ static void mutate(Genome& c, const Block& r, const MutateArgs& a) {
+  template <typename Args>
+  __device__ static void mutate(Genome& c, const Block& r, const Args& a) {
     if (r.z < a.p32) {
       const uint32_t bit = r.w & 63u;
       const uint32_t mask = 1u << (bit & 31u);
