@@ -13,13 +13,15 @@
 //
 // Layout of the work: `normalize_kernel` turns each surface into its retained
 // differentia in rank order (field j, b bits wide, = rank j * 2^e(T)), a
-// 64-bit string (S * b <= 64); for one-bit differentia the pair kernel keeps
-// every 2^(e - e(T))-th bit of each string (stride compaction), XORs them and
+// 64-bit string (S * b <= 64); for one-bit differentia a pair keeps every
+// 2^(e - e(T))-th bit of each string (stride compaction), XORs them and
 // takes the lowest set bit, O(1) per pair; wider fields are compared field by
-// field up to the first mismatch (at most S <= 32 of them). Integer only.
+// field up to the first mismatch (at most S <= 32 of them). The tilted and
+// hybrid policies need no pass of their own (ga_mrca_pairs.hpp). Integer only.
 #include <mutex>
 
 #include "ga_internal.hpp"
+#include "ga_mrca_pairs.hpp"
 
 namespace ga {
 namespace {
@@ -54,25 +56,26 @@ __device__ uint32_t site_of_retained(uint32_t r, uint32_t s) {
   }
 }
 
-__global__ void normalize_kernel(const uint32_t* __restrict__ T, const uint32_t* __restrict__ D,
-                                 uint32_t n, uint32_t s, uint32_t dlog, Normalized* out) {
-  const uint32_t a = blockIdx.x * blockDim.x + threadIdx.x;
+// One wavefront per surface, lane l deciding bit l of the string.
+__global__ __launch_bounds__(256) void normalize_kernel(const uint32_t* __restrict__ T,
+                                                        const uint32_t* __restrict__ D, uint32_t n,
+                                                        uint32_t s, uint32_t dlog,
+                                                        Normalized* out) {
+  const uint32_t a = blockIdx.x * 4u + (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   if (a >= n) return;
+  const uint32_t lane = threadIdx.x & 63u;
   const uint32_t words = (1u << (s + dlog)) >> 5;  // S * b / 32
-  const uint32_t b = 1u << dlog;
-  const unsigned long long fmask = (1ull << b) - 1ull;
   const uint32_t t = T[a];
   const uint32_t e = epoch_of(t, s);
   const uint32_t count = t == 0u ? 0u : ((t - 1u) >> e) + 1u;  // ceil(t / 2^e) <= S
-  const unsigned long long w = (unsigned long long)D[(size_t)a * words] |
-                               (words > 1 ? (unsigned long long)D[(size_t)a * words + 1] << 32
-                                          : 0ull);
-  unsigned long long bits = 0ull;
-  for (uint32_t j = 0; j < count; ++j) {
-    const uint32_t site = site_of_retained(j << e, s);
-    bits |= ((w >> (site << dlog)) & fmask) << (j << dlog);
+  const uint32_t j = lane >> dlog;                             // the bit's field
+  uint32_t bit = 0u;
+  if (j < count) {
+    const uint32_t at = (site_of_retained(j << e, s) << dlog) + (lane & ((1u << dlog) - 1u));
+    bit = (D[(size_t)a * words + (at >> 5)] >> (at & 31u)) & 1u;
   }
-  out[a] = Normalized{bits, t, e};
+  const unsigned long long bits = __builtin_amdgcn_ballot_w64(bit != 0u);
+  if (lane == 0u) out[a] = Normalized{bits, t, e};
 }
 
 // keep bits 0, 2^d, 2*2^d, ... of x, packed to the bottom
@@ -126,209 +129,6 @@ __device__ __forceinline__ uint2 pair_interval(const Normalized& a, const Normal
   return make_uint2(lower, upper);
 }
 
-// One thread per pair (x, y) in each of eight passes over 2,048 consecutive y
-// (256 per pass, lane-consecutive, so loads and the two output rows are
-// coalesced); rows of the grid are x.
-__global__ __launch_bounds__(256) void pairs_kernel(const Normalized* __restrict__ nz, uint32_t n,
-                                                    uint32_t dlog, uint32_t kc,
-                                                    uint32_t* __restrict__ L,
-                                                    uint32_t* __restrict__ U) {
-  const uint32_t x = blockIdx.y;
-  const Normalized a = nz[x];
-  const size_t row = (size_t)x * n;
-#pragma unroll
-  for (uint32_t pass = 0; pass < 8; ++pass) {
-    const uint32_t y = blockIdx.x * 2048u + pass * 256u + threadIdx.x;
-    if (y < n) {
-      const uint2 r = pair_interval(a, nz[y], dlog, kc);
-      U[row + y] = r.y;
-      L[row + y] = r.x;
-    }
-  }
-}
-
-// Tilted surfaces (S = 32 m sites, level k = site / m, slot j = site % m):
-// the rank a slot holds after T deposits is the most recent rank below T of
-// its level whose index along the level is j mod m. A rank sits at one site
-// whatever T is, so the ranks two surfaces share are the slots where both
-// hold the same rank.
-// The rank slot j of level k holds after T deposits, or kNone. Level k < 31
-// holds the odd multiples 2^k (2i + 1), level 31 the multiples i 2^31 (rank 0
-// among them); slot j keeps the newest one below T with i = j mod 2^m_log.
-constexpr uint32_t kNone = 0xFFFFFFFFu;
-__device__ __forceinline__ uint32_t tilted_slot_rank(uint32_t T, uint32_t k, uint32_t j,
-                                                     uint32_t m_log) {
-  if (T == 0u) return kNone;
-  const uint32_t q = (T - 1u) >> k;
-  if (k < 31u && q == 0u) return kNone;
-  const uint32_t imax = k < 31u ? (q - 1u) >> 1 : q;
-  if (imax < j) return kNone;
-  const uint32_t i = imax - ((imax - j) & ((1u << m_log) - 1u));
-  return k < 31u ? ((2u * i + 1u) << k) : (i << 31);
-}
-
-// Tiled pairs for the tilted and hybrid policies. U and L are symmetric in
-// the two surfaces, so a workgroup takes a 64 x 64 block of pairs (rows
-// x0.., columns y0..) only when y0 >= x0 and writes the block and its mirror
-// image. Each lane keeps its column surface's per-site ranks in registers for
-// the 16 rows its wavefront visits (the rank computation is paid once per
-// lane, not once per pair); the rows' ranks are built once per workgroup in
-// LDS and read back as wavefront-uniform broadcasts. The mirror image goes
-// out through an LDS transpose so both writes are whole-row and coalesced.
-constexpr uint32_t kPairTile = 64;
-constexpr uint32_t kRowsPerWave = kPairTile / 4;
-
-struct PairStage {
-  uint32_t u[kPairTile][kPairTile + 1];  // [row in block][column in block]
-  uint32_t l[kPairTile][kPairTile + 1];
-};
-
-// Row r (x = x0 + r) of the block: write (x, y) directly and keep it for the
-// mirror image.
-__device__ __forceinline__ void put_pair(PairStage& st, uint32_t r, uint32_t lane, uint32_t x,
-                                         uint32_t y, uint32_t n, uint32_t u, uint32_t l,
-                                         uint32_t* __restrict__ L, uint32_t* __restrict__ U) {
-  if (x < n && y < n) {
-    const size_t at = (size_t)x * n + y;
-    U[at] = u;
-    L[at] = l;
-  }
-  st.u[r][lane] = u;
-  st.l[r][lane] = l;
-}
-
-// The mirror image of an off-diagonal block: (y, x) for every staged (x, y).
-__device__ __forceinline__ void put_mirror(const PairStage& st, uint32_t x0, uint32_t y0,
-                                           uint32_t n, uint32_t* __restrict__ L,
-                                           uint32_t* __restrict__ U) {
-  const uint32_t lane = threadIdx.x & 63u;
-  const uint32_t wid = (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const uint32_t x = x0 + lane;
-  for (uint32_t c = wid * kRowsPerWave; c < (wid + 1u) * kRowsPerWave; ++c) {
-    const uint32_t y = y0 + c;
-    if (x < n && y < n) {
-      const size_t at = (size_t)y * n + x;
-      U[at] = st.u[lane][c];
-      L[at] = st.l[lane][c];
-    }
-  }
-}
-
-// The kc passes for L over the common ranks cr[site] (kNone: the site is not
-// common). Pass p takes the largest common rank below bound (U on the first
-// pass, then the previous pass's rank) and keeps it plus one; a pass that
-// finds none gives 0, and 0 stays. The last pass's value is L: the kc-th
-// common rank below U, plus one, or 0 when there are fewer. In unsigned
-// arithmetic that value is bound minus the smallest (bound - 1) - cr: a rank
-// at or above the bound wraps to a difference above the bound, and kNone
-// gives exactly bound (nothing found), which is also where the search starts.
-// `STEADY` adds the hybrid's steady half, whose common ranks 2 j 2^E (j < cs)
-// give the largest one below a bound in closed form.
-template <uint32_t S, bool STEADY>
-__device__ __forceinline__ uint32_t kth_common_below(const uint32_t (&cr)[S], uint32_t upper,
-                                                     uint32_t kc, uint32_t cs, uint32_t E) {
-  uint32_t bound = upper, best = 0u;
-  for (uint32_t p = 0; p < kc; ++p) {
-    uint32_t gap = bound;
-    if (STEADY && cs > 0u && bound > 0u) {
-      uint32_t jm = (bound - 1u) >> (E + 1u);  // largest j with 2 j 2^E < bound
-      if (jm > cs - 1u) jm = cs - 1u;
-      gap = bound - (2u * (jm << E) + 1u);
-    }
-    const uint32_t below = bound - 1u;
-#pragma unroll
-    for (uint32_t site = 0; site < S; ++site) {
-      const uint32_t d = below - cr[site];
-      gap = d < gap ? d : gap;
-    }
-    best = bound - gap;
-    bound = best - (best != 0u);
-  }
-  return best;
-}
-
-// All ones where bit `pos` of the word is set, else zero (one bit-field
-// extract, sign-extended; pos is a constant once the site loops unroll).
-__device__ __forceinline__ uint32_t bit_mask_dyn(uint32_t word, uint32_t pos) {
-  return (uint32_t)__builtin_amdgcn_sbfe((int)word, pos, 1);
-}
-
-template <uint32_t S, uint32_t DLOG>
-__global__ __launch_bounds__(256) void pairs_tilted_tile_kernel(const uint32_t* __restrict__ T,
-                                                                const uint32_t* __restrict__ D,
-                                                                uint32_t n, uint32_t kc,
-                                                                uint32_t* __restrict__ L,
-                                                                uint32_t* __restrict__ U) {
-  const uint32_t x0 = blockIdx.y * kPairTile, y0 = blockIdx.x * kPairTile;
-  if (y0 < x0) return;
-  constexpr uint32_t m_log = S == 64u ? 1u : 0u;
-  constexpr uint32_t s_log = S == 64u ? 6u : 5u;
-  constexpr uint32_t words = (S << DLOG) >> 5;
-  __shared__ uint32_t xr[kPairTile][S];
-  __shared__ PairStage st;
-  const uint32_t lane = threadIdx.x & 63u;
-  const uint32_t wid = (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  for (uint32_t e = threadIdx.x; e < kPairTile * S; e += blockDim.x) {
-    const uint32_t r = e >> s_log, site = e & (S - 1u);
-    const uint32_t x = x0 + r;
-    xr[r][site] = tilted_slot_rank(x < n ? T[x] : 0u, site >> m_log, site & ((1u << m_log) - 1u),
-                                   m_log);
-  }
-  const uint32_t y = y0 + lane;
-  const uint32_t yc = y < n ? y : n - 1u;  // a valid surface for lanes past the end
-  const uint32_t tb = T[yc];
-  const unsigned long long wb = (unsigned long long)D[(size_t)yc * words] |
-                                (words > 1 ? (unsigned long long)D[(size_t)yc * words + 1] << 32
-                                           : 0ull);
-  uint32_t rb[S];
-#pragma unroll
-  for (uint32_t site = 0; site < S; ++site)
-    rb[site] = tilted_slot_rank(tb, site >> m_log, site & ((1u << m_log) - 1u), m_log);
-  __syncthreads();
-#pragma unroll 1
-  for (uint32_t i = 0; i < kRowsPerWave; ++i) {
-    const uint32_t r = wid * kRowsPerWave + i, x = x0 + r;
-    const uint32_t xc = x < n ? x : n - 1u;
-    const uint32_t ta = T[xc];
-    const unsigned long long wa = (unsigned long long)D[(size_t)xc * words] |
-                                  (words > 1 ? (unsigned long long)D[(size_t)xc * words + 1] << 32
-                                             : 0ull);
-    unsigned long long diff = wa ^ wb;
-    if (DLOG == 1u) diff |= diff >> 1;  // bit 2 s: field s differs
-    // all ones over the sites whose fields agree: the sign-extended bit of ~diff
-    const uint32_t agree_lo = ~(uint32_t)diff, agree_hi = ~(uint32_t)(diff >> 32);
-    uint32_t upper = ta < tb ? ta : tb;
-    uint32_t cr[S];  // the rank both surfaces hold at the site, or kNone
-#pragma unroll
-    for (uint32_t site = 0; site < S; ++site) {
-      const uint32_t ra = xr[r][site];
-      cr[site] = ra == rb[site] ? ra : kNone;
-      const uint32_t pos = site << DLOG;
-      const uint32_t agree = pos < 32u ? bit_mask_dyn(agree_lo, pos) : bit_mask_dyn(agree_hi, pos - 32u);
-      const uint32_t cand = cr[site] | agree;  // kNone unless common and differing
-      upper = cand < upper ? cand : upper;
-    }
-    put_pair(st, r, lane, x, y, n, upper, kth_common_below<S, false>(cr, upper, kc, 0u, 0u), L,
-             U);
-  }
-  if (x0 == y0) return;
-  __syncthreads();
-  put_mirror(st, x0, y0, n, L, U);
-}
-
-// Steady half of a hybrid surface (sites 0..31 of the low word, (t + 1) / 2
-// deposits on the even ranks) in rank order: bit j is the differentia of its
-// j-th retained deposit, rank j 2^e of the half, e its epoch.
-__device__ __forceinline__ uint32_t steady_half_bits(uint32_t t, uint32_t w_lo, uint32_t* epoch) {
-  const uint32_t nh = (t >> 1) + (t & 1u);
-  const uint32_t e = epoch_of(nh, 5u);
-  const uint32_t count = nh == 0u ? 0u : ((nh - 1u) >> e) + 1u;  // <= 32
-  uint32_t bits = 0u;
-  for (uint32_t j = 0; j < count; ++j) bits |= ((w_lo >> site_of_retained(j << e, 5u)) & 1u) << j;
-  *epoch = e;
-  return bits;
-}
-
 // Keep bits 0, 2^d, 2 * 2^d, ... of a 32-bit string, packed to the bottom.
 __device__ __forceinline__ uint32_t compact_stride32(uint32_t x, uint32_t d) {
   for (uint32_t i = 0; i < d && i < 5u; ++i) {
@@ -341,82 +141,133 @@ __device__ __forceinline__ uint32_t compact_stride32(uint32_t x, uint32_t d) {
   return x;
 }
 
-// Hybrid surfaces, tiled as above: the tilted half's ranks (odd ranks) per
-// lane in registers and per row in LDS; the steady halves in rank order (per
-// lane and per row), so their first differing common rank 2 j 2^E is the
-// lowest set bit of the XOR of the two strings thinned to the common ranks,
-// and the largest of their common ranks below a bound is closed-form.
-__global__ __launch_bounds__(256) void pairs_hybrid_tile_kernel(const uint32_t* __restrict__ T,
-                                                                const uint32_t* __restrict__ D,
-                                                                uint32_t n, uint32_t kc,
-                                                                uint32_t* __restrict__ L,
-                                                                uint32_t* __restrict__ U) {
-  const uint32_t x0 = blockIdx.y * kPairTile, y0 = blockIdx.x * kPairTile;
-  if (y0 < x0) return;
-  __shared__ uint32_t xr[kPairTile][32];
-  __shared__ uint32_t xs[kPairTile][2];  // steady half in rank order, its epoch
-  __shared__ PairStage st;
-  const uint32_t lane = threadIdx.x & 63u;
-  const uint32_t wid = (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  for (uint32_t e = threadIdx.x; e < kPairTile * 32u; e += blockDim.x) {
-    const uint32_t r = e >> 5, k = e & 31u;
-    const uint32_t x = x0 + r;
-    const uint32_t ra = tilted_slot_rank((x < n ? T[x] : 0u) >> 1, k, 0u, 0u);
-    xr[r][k] = ra == kNone ? kNone : 2u * ra + 1u;
-  }
-  if (threadIdx.x < kPairTile) {
-    const uint32_t x = x0 + threadIdx.x;
-    uint32_t e = 0u;
-    xs[threadIdx.x][0] = x < n ? steady_half_bits(T[x], D[(size_t)x * 2], &e) : 0u;
-    xs[threadIdx.x][1] = e;
-  }
-  const uint32_t y = y0 + lane;
-  const uint32_t yc = y < n ? y : n - 1u;
-  const uint32_t tb = T[yc];
-  const unsigned long long wb =
-      (unsigned long long)D[(size_t)yc * 2] | (unsigned long long)D[(size_t)yc * 2 + 1] << 32;
-  uint32_t rb[32];
+// Steady pairs: nothing but writes (8 bytes a pair). One thread per pair (x, y) in
+// each of eight passes over 2,048 consecutive y (256 per pass, lane-consecutive,
+// so loads and the two output rows are coalesced); rows of the grid are x.
+template <bool WIDE>
+__global__ __launch_bounds__(256) void steady_pairs_kernel(const Normalized* __restrict__ nz,
+                                                           uint32_t n, uint32_t dlog, uint32_t kc,
+                                                           uint32_t* __restrict__ L,
+                                                           uint32_t* __restrict__ U) {
+  const uint32_t x = blockIdx.y;
+  const Normalized a = nz[x];
+  const size_t row = (size_t)x * n;
 #pragma unroll
-  for (uint32_t k = 0; k < 32; ++k) {
-    const uint32_t r = tilted_slot_rank(tb >> 1, k, 0u, 0u);
-    rb[k] = r == kNone ? kNone : 2u * r + 1u;
+  for (uint32_t pass = 0; pass < 8; ++pass) {
+    const uint32_t y = blockIdx.x * 2048u + pass * 256u + threadIdx.x;
+    if (y < n) {
+      const uint2 r = pair_interval(a, nz[y], WIDE ? dlog : 0u, kc);
+      U[row + y] = r.y;
+      L[row + y] = r.x;
+    }
   }
-  const uint32_t nb = (tb >> 1) + (tb & 1u);
-  uint32_t eb = 0u;
-  const uint32_t sb = steady_half_bits(tb, (uint32_t)wb, &eb);
+}
+
+// What a pair needs of a surface, in the four words a row or column keeps.
+typedef uint32_t Quad __attribute__((ext_vector_type(4)));
+enum Kind { kTilted, kTilted2, kTiltedWide, kHybrid };
+
+struct PairArgs {
+  const uint32_t* __restrict__ T;
+  const uint32_t* __restrict__ D;
+  uint32_t kc;
+};
+
+// Sites of the hybrid's steady half in rank order, one row of 32 for each of
+// its epochs: 0 to 26, for up to 2^31 deposits.
+constexpr uint32_t kEpochs = 27;
+
+template <int KIND>
+__device__ __forceinline__ Quad surface(const PairArgs& a, uint32_t x, const uint8_t* sites) {
+  const uint32_t t = a.T[x];
+  if (KIND == kTilted) return Quad{a.D[x], 0u, t, 0u};
+  const uint32_t lo = a.D[(size_t)x * 2], hi = a.D[(size_t)x * 2 + 1];
+  if (KIND == kTilted2 || KIND == kTiltedWide) {
+    // slots 0 and 1 of every level, or bits 0 and 1 of every field
+    const uint64_t w = (uint64_t)hi << 32 | lo;
+    return Quad{even_bits(w), even_bits(w >> 1), t, 0u};
+  }
+  // hybrid: the steady half (sites 0..31) in rank order, (t + 1) / 2 deposits
+  // on the even ranks; the tilted half's levels
+  const uint32_t nh = (t >> 1) + (t & 1u);
+  const uint32_t e = epoch_of(nh, 5u);
+  const uint32_t count = nh == 0u ? 0u : ((nh - 1u) >> e) + 1u;  // <= 32
+  uint32_t bits = 0u;
+  for (uint32_t j = 0; j < count; ++j) bits |= ((lo >> sites[e * 32u + j]) & 1u) << j;
+  return Quad{bits, hi, t, e};
+}
+
+template <int KIND>
+__device__ __forceinline__ Interval interval(const PairArgs& g, const Quad& a, const Quad& b) {
+  if (KIND == kTilted) return tilted_interval(a.z, b.z, a.x ^ b.x, g.kc);
+  if (KIND == kTiltedWide) return tilted_interval(a.z, b.z, (a.x ^ b.x) | (a.y ^ b.y), g.kc);
+  if (KIND == kTilted2) return tilted2_interval(a.z, b.z, a.x ^ b.x, a.y ^ b.y, g.kc);
+  const uint32_t E = a.w > b.w ? a.w : b.w;
+  const uint32_t na = (a.z >> 1) + (a.z & 1u), nb = (b.z >> 1) + (b.z & 1u);
+  const uint32_t nmin = na < nb ? na : nb;
+  const uint32_t shared = nmin == 0u ? 0u : ((nmin - 1u) >> E) + 1u;  // <= 32
+  return hybrid_interval(a.z, b.z, compact_stride32(a.x, E - a.w), compact_stride32(b.x, E - b.w),
+                         E, shared, a.y ^ b.y, g.kc);
+}
+
+// All pairs under the tilted and hybrid policies. A workgroup takes `rows`
+// consecutive rows x by 1,024 columns: a thread keeps four columns' surfaces in
+// registers (256 apart, so a store is a wavefront's 256 consecutive bytes) and
+// reads each row's from LDS (one address for the whole wavefront). The writes
+// take 117 to 124 us of a 10,000 x 10,000 matrix (a plain fill of both outputs);
+// with 60 to 230 vector instructions a pair it takes, against comparing all S
+// sites of a pair in mirrored 64 x 64 blocks: tilted S = 32 147 us (601), S = 64
+// 267 (1,164), S = 32 of 2 bits 160 (601), hybrid 505 (858). Bound: the writes,
+// VALU for S = 64 and the hybrid. Four consecutive columns a thread (16-byte
+// stores) or 32 rows measured 2% and 10% slower.
+constexpr uint32_t kCols = 4;  // columns a thread keeps
+constexpr uint32_t kMaxRows = 8;
+
+template <int KIND>
+__global__ __launch_bounds__(256) void pairs_kernel(PairArgs args, uint32_t n, uint32_t rows,
+                                                    uint32_t* __restrict__ L,
+                                                    uint32_t* __restrict__ U) {
+  __shared__ Quad row[kMaxRows];
+  __shared__ uint8_t sites[KIND == kHybrid ? kEpochs * 32u : 1u];
+  const uint32_t x0 = blockIdx.y * rows, x1 = min(x0 + rows, n);
+  if (KIND == kHybrid) {
+    for (uint32_t k = threadIdx.x; k < kEpochs * 32u; k += 256u)
+      sites[k] = (uint8_t)site_of_retained((k & 31u) << (k >> 5), 5u);
+    __syncthreads();
+  }
+  for (uint32_t x = x0 + threadIdx.x; x < x1; x += 256u)
+    row[x - x0] = surface<KIND>(args, x, sites);
+  const uint32_t y = blockIdx.x * (256u * kCols) + threadIdx.x;
+  Quad col[kCols];
+#pragma unroll
+  for (uint32_t c = 0; c < kCols; ++c)
+    col[c] = surface<KIND>(args, min(y + 256u * c, n - 1u), sites);
   __syncthreads();
 #pragma unroll 1
-  for (uint32_t i = 0; i < kRowsPerWave; ++i) {
-    const uint32_t r = wid * kRowsPerWave + i, x = x0 + r;
-    const uint32_t xc = x < n ? x : n - 1u;
-    const uint32_t ta = T[xc];
-    const unsigned long long diff =
-        ((unsigned long long)D[(size_t)xc * 2] | (unsigned long long)D[(size_t)xc * 2 + 1] << 32) ^
-        wb;
-    // steady halves: common ranks 2 j 2^E for j < cs
-    const uint32_t na = (ta >> 1) + (ta & 1u);
-    const uint32_t ea = xs[r][1];
-    const uint32_t E = ea > eb ? ea : eb;
-    const uint32_t nmin = na < nb ? na : nb;
-    const uint32_t cs = nmin == 0u ? 0u : ((nmin - 1u) >> E) + 1u;  // <= 32
-    uint32_t upper = ta < tb ? ta : tb;
-    const uint32_t hit = (compact_stride32(xs[r][0], E - ea) ^ compact_stride32(sb, E - eb)) &
-                         (cs >= 32u ? 0xFFFFFFFFu : (1u << cs) - 1u);
-    if (hit) upper = min(upper, 2u * ((uint32_t)(__ffs(hit) - 1) << E));
-    const uint32_t agree_hi = ~(uint32_t)(diff >> 32);  // tilted half: sites 32..63
-    uint32_t cr[32];  // the odd rank both surfaces hold at the level, or kNone
+  for (uint32_t x = x0; x < x1; ++x) {
+    const Quad a = row[x - x0];
+    const size_t at = (size_t)x * n + y;
 #pragma unroll
-    for (uint32_t k = 0; k < 32; ++k) {
-      const uint32_t ra = xr[r][k];
-      cr[k] = ra == rb[k] ? ra : kNone;
-      const uint32_t cand = cr[k] | bit_mask_dyn(agree_hi, k);  // kNone unless differing
-      upper = cand < upper ? cand : upper;
+    for (uint32_t c = 0; c < kCols; ++c) {
+      const Interval r = interval<KIND>(args, a, col[c]);
+      if (y + 256u * c < n) {
+        U[at + 256u * c] = r.upper;
+        L[at + 256u * c] = r.lower;
+      }
     }
-    put_pair(st, r, lane, x, y, n, upper, kth_common_below<32, true>(cr, upper, kc, cs, E), L, U);
   }
-  if (x0 == y0) return;
-  __syncthreads();
-  put_mirror(st, x0, y0, n, L, U);
+}
+
+// Rows per workgroup: as many as leave about eight workgroups per CU (2,048), so
+// that a small matrix still spreads over the chip.
+template <int KIND>
+hipError_t launch_pairs(const PairArgs& args, uint32_t n, uint32_t* L, uint32_t* U,
+                        hipStream_t stream) {
+  const uint32_t columns = (n + 256u * kCols - 1u) / (256u * kCols);
+  const uint32_t rows = max(1u, min(kMaxRows, (uint32_t)((uint64_t)columns * n / 2048u)));
+  pairs_kernel<KIND><<<dim3(columns, (n + rows - 1u) / rows), dim3(256), 0, stream>>>(
+      args, n, rows, L, U);
+  return hipGetLastError();
 }
 
 }  // namespace
@@ -457,26 +308,23 @@ hipError_t launch_mrca_matrix(const uint32_t* T, const uint32_t* D, uint32_t n, 
                               uint32_t dlog, uint32_t policy, uint32_t kc, void* workspace,
                               uint32_t* L, uint32_t* U, hipStream_t stream) {
   if (n == 0) return hipSuccess;
-  if (policy == 1u || policy == 2u) {
-    const uint32_t tiles = (n + kPairTile - 1u) / kPairTile;
-    const dim3 grid(tiles, tiles);
-    if (policy == 2u)
-      pairs_hybrid_tile_kernel<<<grid, dim3(256), 0, stream>>>(T, D, n, kc, L, U);
-    else if (s_log == 6u && dlog == 0u)
-      pairs_tilted_tile_kernel<64, 0><<<grid, dim3(256), 0, stream>>>(T, D, n, kc, L, U);
-    else if (s_log == 5u && dlog == 0u)
-      pairs_tilted_tile_kernel<32, 0><<<grid, dim3(256), 0, stream>>>(T, D, n, kc, L, U);
-    else if (s_log == 5u && dlog == 1u)
-      pairs_tilted_tile_kernel<32, 1><<<grid, dim3(256), 0, stream>>>(T, D, n, kc, L, U);
-    else
-      return hipErrorInvalidValue;
-    return hipGetLastError();
+  const PairArgs args{T, D, kc};
+  if (policy == 2u) return launch_pairs<kHybrid>(args, n, L, U, stream);
+  if (policy == 1u) {
+    if (s_log == 6u && dlog == 0u) return launch_pairs<kTilted2>(args, n, L, U, stream);
+    if (s_log == 5u && dlog == 0u) return launch_pairs<kTilted>(args, n, L, U, stream);
+    if (s_log == 5u && dlog == 1u) return launch_pairs<kTiltedWide>(args, n, L, U, stream);
+    return hipErrorInvalidValue;
   }
   Normalized* nz = static_cast<Normalized*>(workspace);
-  normalize_kernel<<<dim3((n + 255) / 256), dim3(256), 0, stream>>>(T, D, n, s_log, dlog, nz);
+  normalize_kernel<<<dim3((n + 3) / 4), dim3(256), 0, stream>>>(T, D, n, s_log, dlog, nz);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  pairs_kernel<<<dim3((n + 2047) / 2048, n), dim3(256), 0, stream>>>(nz, n, dlog, kc, L, U);
+  const dim3 grid((n + 2047) / 2048, n);
+  if (dlog == 0u)
+    steady_pairs_kernel<false><<<grid, dim3(256), 0, stream>>>(nz, n, dlog, kc, L, U);
+  else
+    steady_pairs_kernel<true><<<grid, dim3(256), 0, stream>>>(nz, n, dlog, kc, L, U);
   return hipGetLastError();
 }
 
