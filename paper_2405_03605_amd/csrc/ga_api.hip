@@ -213,6 +213,7 @@ struct ga_run {
   Layout lay{};
   hipStream_t stream = nullptr;
   uint8_t* base = nullptr;
+  void* own = nullptr;  // view.cand and view.exchange
   uint64_t gen_host = 0;
   uint32_t ipw = 64;
   bool ipw_set = false;  // islands per wavefront chosen by the caller (not the default)
@@ -492,16 +493,37 @@ void drop_graph(ga_run* r) {
   }
 }
 
-int enqueue_direct(ga_run* r, uint64_t n) {
-  // Streaming launches in slices whose generation offsets fit a 32-bit argument.
+// n generations of the streaming form from the counter's on, and its advance:
+// two generations a launch as far as fours go (two such launches bring the
+// outbox back to the plane the single one reads), the candidates they start
+// from taken from the population first, so nothing is kept from an earlier call.
+hipError_t launch_streaming(const ga_run* r, uint32_t n, hipStream_t s) {
   ga::RunView v = r->view;
+  const bool pairs = v.log2n >= ga::kPairMinLog && (v.cand || !v.migration);
+  const uint32_t fours = pairs ? n & ~3u : 0u;
+  hipError_t e = hipSuccess;
+  if (fours) {
+    // the caller's chunk, or what of it such a launch takes
+    v.ipw = std::min(r->ipw, ga::pair_agents(v.log2n) >> v.log2n);
+    v.ipw -= v.ipw % per_iter(r);
+    v.span = 0u;
+    if (v.migration) e = ga::launch_generation(v, 0u, 1u, 1u, s);
+    v.span = 2u;
+    for (uint32_t g = 0; g < fours && e == hipSuccess; g += 2u)
+      e = ga::launch_generation(v, g, waves_for(r, v.ipw), 1u, s);
+  }
+  v.span = 1u;
   v.ipw = r->ipw;
-  const uint32_t waves = waves_for(r, r->ipw);
+  for (uint32_t g = fours; g < n && e == hipSuccess; ++g)
+    e = ga::launch_generation(v, g, waves_for(r, v.ipw), r->wpg, s);
+  return e == hipSuccess ? ga::launch_advance(v.gen, n, s) : e;
+}
+
+int enqueue_direct(ga_run* r, uint64_t n) {
+  // in slices whose generation offsets fit a 32-bit argument
   while (n > 0) {
     const uint64_t slice = std::min<uint64_t>(n, 1u << 20);
-    for (uint64_t g = 0; g < slice; ++g)
-      GA_HIP(ga::launch_generation(v, (uint32_t)g, waves, r->wpg, r->stream), "generation launch");
-    GA_HIP(ga::launch_advance(v.gen, slice, r->stream), "advance launch");
+    GA_HIP(launch_streaming(r, (uint32_t)slice, r->stream), "generation launch");
     n -= slice;
   }
   return GA_OK;
@@ -514,14 +536,8 @@ int ensure_graph(ga_run* r) {
   drop_graph(r);
   if (!r->capture_stream)
     GA_HIP(hipStreamCreateWithFlags(&r->capture_stream, hipStreamNonBlocking), "capture stream");
-  ga::RunView v = r->view;
-  v.ipw = r->ipw;
-  const uint32_t waves = waves_for(r, r->ipw);
   GA_HIP(hipStreamBeginCapture(r->capture_stream, hipStreamCaptureModeThreadLocal), "begin capture");
-  hipError_t err = hipSuccess;
-  for (uint32_t g = 0; g < r->graph_block && err == hipSuccess; ++g)
-    err = ga::launch_generation(v, g, waves, r->wpg, r->capture_stream);
-  if (err == hipSuccess) err = ga::launch_advance(v.gen, r->graph_block, r->capture_stream);
+  hipError_t err = launch_streaming(r, r->graph_block, r->capture_stream);
   hipGraph_t graph = nullptr;
   hipError_t end = hipStreamEndCapture(r->capture_stream, &graph);
   if (err != hipSuccess) {
@@ -619,12 +635,12 @@ size_t ga_state_bytes(const ga_config* cfg) {
 
 namespace {
 
-// The exchange area of the LDS-resident form: the library's own small
-// allocation for a run that may be stepped by itself and whose population could
-// fit the GPU's LDS. Without it (no memory left) the form runs one
-// generation per launch. Allocated here, not on the first step, so that a step
-// can be captured.
-void alloc_exchange(ga_run* r) {
+// What a run that may be stepped by itself has beside the caller's memory: the
+// candidates of the streaming form, and the exchange area of the LDS-resident one
+// where the population could fit the GPU's LDS. One small allocation of the
+// library's own; without it (no memory left) the forms run one generation per
+// launch. Made here, not on the first step, so that a step can be captured.
+void alloc_own(ga_run* r) {
   ga::RunView& v = r->view;
   int device = 0, cus = 0;
   if (hipGetDevice(&device) != hipSuccess ||
@@ -632,14 +648,19 @@ void alloc_exchange(ga_run* r) {
     return;
   const bool strings = ga::model_has_string_host(v.model);
   const size_t agent_bytes = 4 * (size_t)(2 + v.words + (strings ? 2 : 0));
-  if (v.agents * agent_bytes > (size_t)cus * kMaxGroupLds) return;
-  const size_t bytes = 2 * (size_t)v.islands * ga::exchange_words(strings) * 8;
+  const size_t cand = 2 * (size_t)v.island_stride * v.ob_stride * 4;
+  const bool resident = v.agents * agent_bytes <= (size_t)cus * kMaxGroupLds;
+  const size_t exchange =
+      resident ? 2 * (size_t)v.islands * ga::exchange_words(strings) * 8 : 0;
   void* p = nullptr;
-  if (hipMalloc(&p, bytes) != hipSuccess) {
+  if (hipMalloc(&p, cand + exchange) != hipSuccess) {
     (void)hipGetLastError();
     return;
   }
-  v.exchange = static_cast<unsigned long long*>(p);
+  r->own = p;
+  v.cand = static_cast<uint32_t*>(p);
+  if (resident)
+    v.exchange = reinterpret_cast<unsigned long long*>(static_cast<uint8_t*>(p) + cand);
 }
 
 // Empty the exchange area of a run at generation t.
@@ -715,13 +736,13 @@ int init_run(const ga_config* cfg, void* dev_mem, size_t bytes, void* hip_stream
   hipError_t e = ga::launch_fill(reinterpret_cast<uint32_t*>(b), 0u, lay.total / 4, r->stream);
   if (e == hipSuccess) e = ga::launch_init(v, r->stream);
   if (e == hipSuccess && alone && !async && v.migration) {
-    alloc_exchange(r);
+    alloc_own(r);
     e = clear_exchange(v, 0, r->stream);
   }
   if (e != hipSuccess) {
-    if (v.exchange) {
+    if (r->own) {
       (void)hipStreamSynchronize(r->stream);
-      (void)hipFree(v.exchange);
+      (void)hipFree(r->own);
     }
     delete r;
     return hip_fail(e, "init fill");
@@ -1083,7 +1104,7 @@ void ga_destroy(ga_run* r) {
   (void)hipStreamSynchronize(r->stream);
   drop_graph(r);
   if (r->capture_stream) (void)hipStreamDestroy(r->capture_stream);
-  if (r->view.exchange) (void)hipFree(r->view.exchange);
+  if (r->own) (void)hipFree(r->own);
   delete r;
 }
 

@@ -290,6 +290,20 @@ __device__ __forceinline__ void drain_memory() {
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 }
 
+// A kernel's dynamic LDS by byte offset (it starts at 0: no kernel that uses
+// these has any other).
+template <typename T>
+__device__ __forceinline__ T lds_get(uint32_t byte) {
+  return *(__attribute__((address_space(3))) T*)byte;
+}
+template <typename T>
+__device__ __forceinline__ void lds_put(uint32_t byte, T x) {
+  *(__attribute__((address_space(3))) T*)byte = x;
+}
+// Keeps the compiler from moving memory accesses across it (the LDS executes a
+// wavefront's accesses in order by itself).
+__device__ __forceinline__ void keep_order() { asm volatile("" ::: "memory"); }
+
 // The dispatcher hands workgroups to the eight XCDs in turn (group g to XCD
 // g mod 8), each XCD with its own L2. Renumbering the groups so that every XCD
 // takes one contiguous band of the grid keeps an island's four neighbours, and

@@ -69,7 +69,28 @@ struct RunView {
   // (g << 1) | bit k of the direction (bits 0 and 1)
   uint32_t tile_w, tile_h, tiles_x, tiles_y;
   unsigned long long* exchange;
+  // streaming form, two generations a launch: the candidates, island i's of
+  // generation t in cand[((t >> 1 & 1) * island_stride + i) * ob_stride + k], k as
+  // in an outbox entry (no header); NULL without them
+  uint32_t* cand;
+  // what a streaming launch does: 1 one generation, 2 two, 0 nothing but leave
+  // the candidates of the generation it is given
+  uint32_t span;
 };
+
+// Streaming launches of two generations: a wavefront's chunk is 16 islands, four
+// lanes to each, but at most 512 agents, in LDS planes of one word per agent with
+// a 64-bit product per island behind them. Chunks are whole iterations of 64
+// agents, so islands of fewer than four (64 / N > 16) have no such launch.
+constexpr uint32_t kPairMinLog = 2;
+constexpr uint32_t pair_words(uint32_t words, bool strings) {
+  return 2u + words + (strings ? 2u : 0u);
+}
+constexpr uint32_t pair_agents(uint32_t log2n) { return log2n < 5u ? 16u << log2n : 512u; }
+constexpr uint32_t pair_plane(uint32_t log2n) {
+  return log2n < 4u ? 1024u : 4u * pair_agents(log2n);
+}
+constexpr uint32_t pair_bytes(uint32_t log2n, uint32_t kw) { return kw * pair_plane(log2n) + 256u; }
 
 // 64-bit words of an exchange slot, and what an empty slot's halves hold while
 // the run is at generation t: no generation a launch from t on waits for.

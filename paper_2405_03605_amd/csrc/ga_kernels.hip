@@ -20,7 +20,11 @@
 // wavefront reads all of an island's agents before it writes any child, and no
 // other wavefront reads them. Population and outbox planes are padded past the
 // last island, so iterations never need a tail predicate.
-#include "ga_device.hpp"
+//
+// Runs stepped by four generations and more take two per launch instead
+// (ga_pair.hpp); this kernel has what is left over, islands of fewer than four
+// members, batches and the asynchronous schedule.
+#include "ga_pair.hpp"
 
 namespace ga {
 namespace {
@@ -504,6 +508,21 @@ __global__ __launch_bounds__(1024) void generation_kernel(RunView v, uint32_t ge
                                                 wave_lds(wig, v.ipw, Model::kString ? 2u : 1u));
 }
 
+// Two generations from the one at `gen_offset` on (ga_pair.hpp); the outbox plane
+// changes with every such launch since the counter was last written.
+template <bool PLAIN, int LC, int SWC, typename Model, bool WIDE>
+__global__ __launch_bounds__(64) void pair_kernel(RunView v, uint32_t gen_offset) {
+  const uint32_t base = xcd_band_group() * v.ipw;
+  const uint64_t t0 = *v.gen;
+  chunk_pair<LC, SWC, Model, WIDE, PLAIN>(v, base, t0 + gen_offset,
+                                   ((uint32_t)t0 ^ 1u ^ (gen_offset >> 1)) & 1u);
+}
+
+__global__ void candidate_kernel(RunView v, uint32_t gen_offset) {
+  const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < v.islands) leave_candidate(v, i, *v.gen + gen_offset);
+}
+
 // Founders of a genome model that draws them (the initialize function): its
 // initialize from the (slot, island) block of the sampling stream at
 // generation 2^64 - 1, which no generation reaches.
@@ -752,11 +771,34 @@ size_t lds_bytes(uint32_t ipw, uint32_t waves, uint32_t model) {
   return (5u * ipw + 1u) * sizeof(uint4) * (model_has_string(model) ? 2u : 1u) * waves;
 }
 
+namespace {
+bool is_plain(const RunView& v) { return v.k == 2u && v.selection && !v.law; }
+}  // namespace
+
 hipError_t launch_generation(const RunView& v, uint32_t gen_offset, uint32_t waves,
                              uint32_t waves_per_group, hipStream_t stream) {
   if (waves == 0) return hipSuccess;
   const uint32_t groups = (waves + waves_per_group - 1) / waves_per_group;
   const dim3 grid(groups), block(64 * waves_per_group);
+  if (v.span == 0u) {
+    candidate_kernel<<<dim3((v.islands + 255u) / 256u), dim3(256), 0, stream>>>(v, gen_offset);
+    return hipGetLastError();
+  }
+  if (v.span == 2u)
+    return dispatch(v, [&](auto LC, auto SWC, auto M, auto WD) {
+      constexpr uint32_t L = decltype(LC)::value;
+      constexpr uint32_t kw = pair_words(decltype(SWC)::value, decltype(M)::kString);
+      if constexpr (L >= kPairMinLog) {
+        if (is_plain(v))
+          pair_kernel<true, GA_SHAPE_ARGS(LC, SWC, M, WD)>
+              <<<dim3(waves), dim3(64), pair_bytes(L, kw), stream>>>(v, gen_offset);
+        else
+          pair_kernel<false, GA_SHAPE_ARGS(LC, SWC, M, WD)>
+              <<<dim3(waves), dim3(64), pair_bytes(L, kw), stream>>>(v, gen_offset);
+        return hipGetLastError();
+      }
+      return hipErrorInvalidValue;
+    });
   const size_t lds = lds_bytes(v.ipw, waves_per_group, v.model);
   return dispatch(v, [&](auto LC, auto SWC, auto M, auto WD) {
     generation_kernel<GA_SHAPE_ARGS(LC, SWC, M, WD)><<<grid, block, lds, stream>>>(v, gen_offset);

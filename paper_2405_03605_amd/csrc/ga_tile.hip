@@ -89,21 +89,7 @@ __host__ __device__ inline uint32_t tile_table_words(uint32_t ta, uint32_t log2n
   return (2u * ((ta + (log2n < 3u ? 64u : 0u)) >> log2n) + 3u) & ~3u;
 }
 
-// The tile's LDS by byte offset (the kernel has no other LDS, so its dynamic
-// part starts at 0).
-template <typename T>
-__device__ __forceinline__ T lds_get(uint32_t byte) {
-  return *(__attribute__((address_space(3))) T*)byte;
-}
-template <typename T>
-__device__ __forceinline__ void lds_put(uint32_t byte, T x) {
-  *(__attribute__((address_space(3))) T*)byte = x;
-}
 typedef uint32_t Quad __attribute__((ext_vector_type(4)));
-
-// Keeps the compiler from moving memory accesses across it (the LDS executes a
-// wavefront's accesses in order by itself).
-__device__ __forceinline__ void keep_order() { asm volatile("" ::: "memory"); }
 
 // Members in LDS: `at` is the byte offset of the member's fitness.
 template <int SW, bool STR>

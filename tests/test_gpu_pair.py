@@ -1,0 +1,82 @@
+"""Streaming launches of two generations, bit for bit against the oracle: chunks
+that straddle several rows, cover more than one pass of islands, end past the
+last island or come short of a wavefront's planes; every policy, string model
+and tournament size; from generations of every remainder by four, in one step,
+in captured blocks and over an outbox and a population set from outside."""
+import pytest
+
+import oracle
+from gpu_helpers import assert_same_state, oracle_after, say
+from paper_2405_03605_amd import FORM_STREAMING, GARun
+from paper_2405_03605_amd.workloads import run_config
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    torch.cuda.set_device(0)
+    yield
+    torch.cuda.synchronize()
+
+
+# configuration, islands per wavefront (0: the default), wavefronts per group
+SHAPES = [
+    (dict(width=1, height=1, pop=32, sites=32, k=2, seed=61), 0, 1),
+    (dict(width=2, height=3, pop=64, sites=64, k=7, seed=62), 1, 16),
+    (dict(width=5, height=67, pop=32, sites=32, k=2, seed=63), 16, 4),
+    (dict(width=70, height=9, pop=1, sites=32, k=1, seed=64), 64, 3),
+    (dict(width=33, height=31, pop=2, sites=64, k=3, seed=65), 32, 4),
+    (dict(width=19, height=45, pop=4, sites=32, k=4, policy=1, seed=66), 48, 2),
+    (dict(width=64, height=32, pop=8, sites=32, k=2, seed=67), 64, 16),
+    (dict(width=47, height=40, pop=16, sites=64, k=5, policy=2, seed=68), 0, 4),
+    (dict(width=63, height=33, pop=32, sites=32, k=2, model=1, seed=69), 0, 4),
+    (dict(width=37, height=41, pop=64, sites=64, k=2, model=2, policy=1, seed=70), 64, 4),
+    (dict(width=29, height=30, pop=16, sites=32, k=6, model=2, seed=71), 40, 5),
+    (dict(width=40, height=30, pop=32, sites=32, k=2, migration=0, seed=72), 0, 4),
+    (dict(width=40, height=30, pop=32, sites=64, k=2, selection=0, seed=73), 0, 4),
+    (dict(width=40, height=30, pop=32, sites=32, k=2, law=1, p_ben32=12884902,
+          p32=1417339207, seed=74), 0, 4),
+    (dict(width=40, height=30, pop=32, sites=16, dbits=4, k=3, seed=76), 0, 4),
+    (dict(width=40, height=30, pop=16, sites=8, dbits=4, k=2, model=1, seed=77), 0, 4),
+]
+
+
+@pytest.mark.parametrize("edge,ipw,wpg", SHAPES,
+                         ids=lambda e: "-".join(f"{k}{v}" for k, v in e.items())
+                         if isinstance(e, dict) else str(e))
+def test_pairs_match_oracle(edge, ipw, wpg):
+    cfg = run_config(**edge)
+    say(f"pairs ipw {ipw} wpg {wpg} on {cfg}")
+    run = GARun(cfg)
+    run.set_launch(ipw, wpg, FORM_STREAMING)
+    run.set_graph_block(0)
+    for n in (4, 1, 9, 14):
+        run.step(n)
+    run.set_graph_block(10)
+    run.step(33)
+    assert_same_state(run.read(), oracle_after(cfg, 61), f"pairs {edge}")
+    run.close()
+
+
+def test_pairs_from_a_state_set_from_outside():
+    cfg = run_config(width=48, height=40, pop=32, sites=32, k=2, seed=75)
+    say(f"pairs from a written state, {cfg}")
+    run = GARun(cfg)
+    run.set_launch(form=FORM_STREAMING)
+    run.step(22)
+    snap = run.read()
+    run.step(8)
+    run.write(snap["f"], snap["T"], snap["D"], snap["outbox"], 7)
+    run.step(30)
+    ref = oracle.OracleRun(cfg)
+    ref.set_population(snap["f"], snap["T"], snap["D"])
+    ob = snap["outbox"]
+    ref.set_outbox(ob["valid"], ob["dir"], ob["f"], ob["T"], ob["D"])
+    ref.set_generation(7)
+    ref.step(30)
+    assert_same_state(run.read(), ref, "pairs set back")
+    run.close()
