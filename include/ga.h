@@ -277,6 +277,11 @@ void ga_destroy(ga_run* run);
  * most 64; default 16, or fewer for small grids) and wavefronts per workgroup
  * (1..16; default 4) of the streaming form, and the launch form. 0 keeps the
  * current value of the first two. Results do not depend on any of these.
+ * Steps of four generations and more take two per launch (islands of four agents
+ * and more), in workgroups of one wavefront with at most 16 islands and 512
+ * agents of the chunk; ga_init allocates what these launches pass on to each
+ * other (32 bytes an island, 64 with 64 sites or a genome string), and without
+ * it every launch takes one generation.
  * GA_EINVAL if a streaming workgroup's LDS table (5 * islands_per_wave + 1
  * entries of 16 bytes, 32 with a genome string, per wavefront) would exceed
  * the 160 KiB of a CU, or if the resident form is asked for a run with no
@@ -392,7 +397,10 @@ int ga_batch_set_graph_block(ga_batch* batch, uint32_t gens_per_block);
  * (0 = the default, 512/N for each member: about 512 agents per wavefront;
  * rounded down to a multiple of 64/N, at most 64) and
  * wavefronts per workgroup (1..16; 0 keeps the current value, default 4).
- * Results do not depend on either. */
+ * Where every member's islands have four agents or more, launches take two
+ * generations: workgroups of one wavefront, chunks of at most 16 islands and 512
+ * agents of that, and by default shorter ones for few members. Results do not
+ * depend on any of it. */
 int ga_batch_set_launch(ga_batch* batch, uint32_t islands_per_wave, uint32_t waves_per_group);
 /* Islands per wavefront of one class of members (log2 N in 0..6, surface
  * words 1 or 2), overriding ga_batch_set_launch for it: 0 = the batch's

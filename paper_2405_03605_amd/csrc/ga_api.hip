@@ -259,6 +259,13 @@ struct ga_batch {
   // the launch the graph was captured with: wavefronts covered (with
   // headroom), largest islands per wavefront (sizes the LDS), group size
   uint32_t grid_waves = 0, use_max_ipw = 0, use_wpg = 0;
+  // whether its launches take two generations: every member's islands have four
+  // agents or more, and its candidates (its own, or in d_cand for a pool's run)
+  // have a place. They are taken anew in each block, so the table's rebuild may
+  // place them elsewhere.
+  bool pairs = false;
+  uint8_t* d_cand = nullptr;
+  size_t cand_cap = 0;
   bool dirty = true;           // membership or shapes changed since the last upload
   bool graph_stale = true;     // the captured graph no longer matches
   hipStream_t capture_stream = nullptr;
@@ -334,15 +341,25 @@ void pool_give(ga_pool* p, size_t off, size_t size) {
 
 uint32_t per_iter(const ga_run* r) { return 64u >> r->view.log2n; }
 
+constexpr uint32_t kFullWaves = 4096;
+
 // Default islands per wavefront: 16 (measured best for large grids on
 // MI355X), fewer when that leaves under 4 wavefronts per SIMD (1024 SIMDs),
 // never fewer than one iteration's worth (64/N islands).
 uint32_t default_ipw(const ga::RunView& v) {
   const uint32_t g = 64u >> v.log2n;
   uint32_t ipw = 16;
-  while (ipw > g && (v.islands + ipw - 1) / ipw < 4096) ipw >>= 1;
+  while (ipw > g && (v.islands + ipw - 1) / ipw < kFullWaves) ipw >>= 1;
   return std::max(g, std::min(64u, ipw));
 }
+
+// Of a chunk of v.ipw islands what a launch of two generations takes (in whole
+// iterations), and the bytes of a run's candidates.
+uint32_t pair_ipw(const ga::RunView& v) {
+  const uint32_t ipw = std::min(v.ipw, ga::pair_agents(v.log2n) >> v.log2n);
+  return ipw - ipw % (64u >> v.log2n);
+}
+size_t cand_bytes(const ga::RunView& v) { return 2 * (size_t)v.island_stride * v.ob_stride * 4; }
 
 uint32_t waves_for(const ga_run* r, uint32_t ipw) {
   return (r->view.islands + ipw - 1) / ipw;
@@ -503,9 +520,8 @@ hipError_t launch_streaming(const ga_run* r, uint32_t n, hipStream_t s) {
   const uint32_t fours = pairs ? n & ~3u : 0u;
   hipError_t e = hipSuccess;
   if (fours) {
-    // the caller's chunk, or what of it such a launch takes
-    v.ipw = std::min(r->ipw, ga::pair_agents(v.log2n) >> v.log2n);
-    v.ipw -= v.ipw % per_iter(r);
+    v.ipw = r->ipw;
+    v.ipw = pair_ipw(v);
     v.span = 0u;
     if (v.migration) e = ga::launch_generation(v, 0u, 1u, 1u, s);
     v.span = 2u;
@@ -648,7 +664,7 @@ void alloc_own(ga_run* r) {
     return;
   const bool strings = ga::model_has_string_host(v.model);
   const size_t agent_bytes = 4 * (size_t)(2 + v.words + (strings ? 2 : 0));
-  const size_t cand = 2 * (size_t)v.island_stride * v.ob_stride * 4;
+  const size_t cand = cand_bytes(v);
   const bool resident = v.agents * agent_bytes <= (size_t)cus * kMaxGroupLds;
   const size_t exchange =
       resident ? 2 * (size_t)v.islands * ga::exchange_words(strings) * 8 : 0;
@@ -1294,6 +1310,7 @@ void to_table(ga::RunView& v, const void* table) {
   v.ob[1] = table_offset(v.ob[1], table);
   v.gen = table_offset(v.gen, table);
   v.left = table_offset(v.left, table);
+  v.cand = table_offset(v.cand, table);
 }
 }  // namespace
 }  // extern "C++"
@@ -1363,9 +1380,55 @@ int rebuild_tables(ga_batch* b) {
   std::vector<ga::Tile> tiles;
   views.reserve(b->members.size());
   uint32_t max_ipw = 1;
+  bool pairs = true;
+  size_t need = 0, placed = 0;
+  for (const ga_run* r : b->members) {
+    if (r->view.log2n < ga::kPairMinLog) pairs = false;
+    if (r->view.migration && !r->view.cand) need += cand_bytes(r->view);
+  }
+  if (pairs && need > b->cand_cap) {
+    GA_HIP(hipStreamSynchronize(b->stream), "stream sync");
+    if (b->d_cand) GA_HIP(hipFree(b->d_cand), "free candidates");
+    b->d_cand = nullptr;
+    b->cand_cap = 0;
+    void* p = nullptr;
+    if (hipMalloc(&p, 2 * need) == hipSuccess) {
+      b->d_cand = static_cast<uint8_t*>(p);
+      b->cand_cap = 2 * need;
+    } else {
+      (void)hipGetLastError();
+      pairs = false;  // no memory left: one generation per launch
+    }
+  }
+  if (pairs != b->pairs) b->graph_stale = true;
+  b->pairs = pairs;
+  // chunks as for a run alone: where that leaves under 4 wavefronts per SIMD,
+  // classes without a setting of their own take shorter ones, down to one
+  // iteration (24 requests through 16 slots: 28.2 ms at full chunks, 24.5, 23.9,
+  // 22.9 and 23.9 with at least 1024, 2048, 4096 and 8192 wavefronts)
+  auto chunk = [&](const ga::RunView& view, uint32_t halvings) {
+    ga::RunView v = view;
+    v.ipw = class_ipw(b, class_of(v));
+    if (!pairs) return v.ipw;
+    v.ipw = pair_ipw(v);
+    if (b->ipw_override || b->cls[class_of(v)].ipw) return v.ipw;
+    return std::max(64u >> v.log2n, v.ipw >> halvings);
+  };
+  uint32_t halvings = 0;
+  for (; pairs && halvings < 4; ++halvings) {
+    uint64_t waves = 0;
+    for (const ga_run* r : b->members)
+      waves += ceil_div(r->view.islands, chunk(r->view, halvings));
+    if (waves >= kFullWaves) break;
+  }
+  const uint32_t wpg = pairs ? 1u : b->wpg;
   for (uint32_t m = 0; m < b->members.size(); ++m) {
     ga::RunView v = b->members[m]->view;
-    v.ipw = class_ipw(b, class_of(v));
+    v.ipw = chunk(v, halvings);
+    if (pairs && v.migration && !v.cand) {
+      v.cand = reinterpret_cast<uint32_t*>(b->d_cand + placed);
+      placed += cand_bytes(v);
+    }
     max_ipw = std::max(max_ipw, v.ipw);
     views.push_back(v);
     for (uint32_t first = 0; first < v.islands; first += v.ipw)
@@ -1378,13 +1441,13 @@ int rebuild_tables(ga_batch* b) {
   for (BatchClass& k : b->cls) k.n_tiles = 0;
   for (const ga::Tile& t : tiles) b->cls[t.cls].n_tiles += 1;
   std::vector<uint32_t> slot;
-  const uint32_t span = place_tiles(views, tiles, b->wpg, slot);
+  const uint32_t span = place_tiles(views, tiles, wpg, slot);
   // the graph's grid covers the placement with headroom; it is captured
   // again only when a placement outgrows it or the launch shape changes (the
   // largest islands per wavefront sizes each wavefront's LDS)
-  const uint32_t unit = 8u * b->wpg;  // whole groups on every XCD
+  const uint32_t unit = 8u * wpg;  // whole groups on every XCD
   uint32_t grid = b->grid_waves;
-  if (span > grid || b->wpg != b->use_wpg)
+  if (span > grid || wpg != b->use_wpg)
     grid = ceil_div(std::max(grid, pow2_at_least(span)), unit) * unit;
   if (views.size() > b->view_cap || grid > b->tile_cap || !b->d_tab) {
     GA_HIP(hipStreamSynchronize(b->stream), "stream sync");
@@ -1417,9 +1480,9 @@ int rebuild_tables(ga_batch* b) {
   counts[1] = (uint32_t)views.size();
   if (grid != b->grid_waves) b->graph_stale = true;
   b->grid_waves = grid;
-  if (max_ipw != b->use_max_ipw || b->wpg != b->use_wpg) b->graph_stale = true;
+  if (max_ipw != b->use_max_ipw || wpg != b->use_wpg) b->graph_stale = true;
   b->use_max_ipw = max_ipw;
-  b->use_wpg = b->wpg;
+  b->use_wpg = wpg;
   GA_HIP(hipMemcpyAsync(b->d_tab, st, b->stage_bytes, hipMemcpyHostToDevice, b->stream),
          "upload tables");
   GA_HIP(hipEventRecord(b->stage_done[b->stage_next], b->stream), "staging event");
@@ -1443,20 +1506,48 @@ hipError_t launch_gen(ga_batch* b, uint32_t gen_offset, hipStream_t s) {
                               b->use_max_ipw, b->use_wpg, s);
 }
 
-int batch_direct(ga_batch* b, uint64_t n) {
+// The launches of n generations that every block has: where two go at a time,
+// the candidates and the pairs of a member that has n to go.
+hipError_t launch_block(ga_batch* b, uint32_t n, hipStream_t s) {
+  hipError_t e = hipSuccess;
+  if (!b->pairs) {
+    for (uint32_t g = 0; g < n && e == hipSuccess; ++g) e = launch_gen(b, g, s);
+    return e;
+  }
+  const uint32_t fours = n & ~3u;
+  if (fours) e = launch_gen(b, ga::kBatchCandidates, s);
+  for (uint32_t g = 0; g < fours && e == hipSuccess; g += 2u) e = launch_gen(b, ga::kBatchPair | g, s);
+  return e;
+}
+
+// And what closes the block `ran` generations into a step call: the single
+// generations that some member has left over, and the members' advance.
+int close_block(ga_batch* b, uint32_t n, uint64_t ran) {
+  uint64_t singles = 0;
+  for (uint64_t r : b->remaining)
+    if (r > ran) singles = std::max(singles, std::min<uint64_t>(r - ran, n) & 3u);
+  if (!b->pairs) singles = 0;
+  for (uint32_t s = 0; s < singles; ++s)
+    GA_HIP(launch_gen(b, ga::batch_single(n, s), b->stream), "batch launch");
+  GA_HIP(ga::launch_batch_advance(tab_views(b), tab_count(b, 1), b->view_cap, n, b->stream),
+         "batch advance");
+  return GA_OK;
+}
+
+int batch_direct(ga_batch* b, uint64_t n, uint64_t ran) {
   while (n > 0) {
     const uint64_t slice = std::min<uint64_t>(n, 1u << 20);
-    for (uint64_t g = 0; g < slice; ++g)
-      GA_HIP(launch_gen(b, (uint32_t)g, b->stream), "batch launch");
-    GA_HIP(ga::launch_batch_advance(tab_views(b), tab_count(b, 1), b->view_cap, slice, b->stream),
-           "batch advance");
+    GA_HIP(launch_block(b, (uint32_t)slice, b->stream), "batch launch");
+    const int rc = close_block(b, (uint32_t)slice, ran);
+    if (rc != GA_OK) return rc;
     n -= slice;
+    ran += slice;
   }
   return GA_OK;
 }
 
-// One block of graph_block generations: one launch per generation over every
-// member's tiles, then the block's advance. Members are read from the device
+// One block of graph_block generations: the launches over every member's tiles
+// that launch_block names. Members are read from the device
 // tables at run time, so the graph outlives membership changes.
 int batch_graph(ga_batch* b) {
   if (b->graph && !b->graph_stale) return GA_OK;
@@ -1470,12 +1561,7 @@ int batch_graph(ga_batch* b) {
   if (!b->capture_stream)
     GA_HIP(hipStreamCreateWithFlags(&b->capture_stream, hipStreamNonBlocking), "capture stream");
   GA_HIP(hipStreamBeginCapture(b->capture_stream, hipStreamCaptureModeThreadLocal), "begin capture");
-  hipError_t err = hipSuccess;
-  for (uint32_t g = 0; g < b->graph_block && err == hipSuccess; ++g)
-    err = launch_gen(b, g, b->capture_stream);
-  if (err == hipSuccess)
-    err = ga::launch_batch_advance(tab_views(b), tab_count(b, 1), b->view_cap, b->graph_block,
-                                   b->capture_stream);
+  hipError_t err = launch_block(b, b->graph_block, b->capture_stream);
   hipGraph_t graph = nullptr;
   hipError_t end = hipStreamEndCapture(b->capture_stream, &graph);
   if (err != hipSuccess) {
@@ -1516,16 +1602,20 @@ int ga_batch_step(ga_batch* b, uint64_t n) {
     if (rc != GA_OK) return rc;
   }
   uint64_t left = n;
-  if (b->graph_block > 0 && left >= b->graph_block) {
+  // (a block of pairs too short for one has nothing to capture)
+  const bool graph = b->pairs ? b->graph_block >= 4u : b->graph_block > 0u;
+  if (graph && left >= b->graph_block) {
     int rc = batch_graph(b);
     if (rc != GA_OK) return rc;
     while (left >= b->graph_block) {
       const Range block("batch block", b->graph_block);
       GA_HIP(hipGraphLaunch(b->graph, b->stream), "graph launch");
+      rc = close_block(b, b->graph_block, n - left);
+      if (rc != GA_OK) return rc;
       left -= b->graph_block;
     }
   }
-  int rc = batch_direct(b, left);
+  int rc = batch_direct(b, left, n - left);
   if (rc != GA_OK) return rc;
   // host mirrors: however the n generations are split into blocks, each
   // member advances by min(n, its remaining budget)
@@ -1564,6 +1654,7 @@ void ga_batch_destroy(ga_batch* b) {
     if (b->stage_done[i]) (void)hipEventDestroy(b->stage_done[i]);
   }
   if (b->d_tab) (void)hipFree(b->d_tab);
+  if (b->d_cand) (void)hipFree(b->d_cand);
   delete b;
 }
 

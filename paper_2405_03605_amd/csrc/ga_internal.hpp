@@ -165,9 +165,17 @@ hipError_t launch_fill(uint32_t* p, uint32_t value, size_t words, hipStream_t st
 hipError_t launch_sample(const RunView& v, uint32_t* ids, hipStream_t stream);
 hipError_t launch_gather(const RunView& v, const uint32_t* ids, uint32_t n, uint32_t* T_out,
                          uint32_t* D_out, hipStream_t stream);
-// One generation of a batch: grid_waves wavefronts, wavefront w running
-// tiles[w] (the table holds grid_waves slots; an empty one has class
-// kNoTile); LDS sized for max_ipw.
+// One launch of a batch: grid_waves wavefronts, wavefront w running tiles[w]
+// (the table holds grid_waves slots; an empty one has class kNoTile); LDS sized
+// for max_ipw. `gen_offset` is the block's generation that it runs, or one of
+// the launches of a block of n generations run two at a time, in which a member
+// with `left` generations to go takes min(left, n), as far as fours go by the
+// first kind and up to three singles after:
+//   kBatchPair | g      generations g and g + 1 (g even)
+//   batch_single(n, s)  the s-th single one
+//   kBatchCandidates    none; leaves the candidates the first pair starts from
+constexpr uint32_t kBatchPair = 1u << 30, kBatchSingle = 2u << 30, kBatchCandidates = 3u << 30;
+constexpr uint32_t batch_single(uint32_t n, uint32_t s) { return kBatchSingle | (n << 2) | s; }
 hipError_t launch_batch_all(const RunView* views, const Tile* tiles, uint32_t grid_waves,
                             uint32_t gen_offset, uint32_t max_ipw, uint32_t waves_per_group,
                             hipStream_t stream);

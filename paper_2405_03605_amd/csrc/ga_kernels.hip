@@ -670,6 +670,7 @@ __device__ __forceinline__ void from_table(RunView& v, const RunView* table) {
   v.ob[1] = table_ptr(table, v.ob[1]);
   v.gen = table_ptr(table, v.gen);
   v.left = table_ptr(table, v.left);
+  v.cand = table_ptr(table, v.cand);
 }
 
 // Memory that stays unchanged for a whole launch (the member table, a
@@ -710,7 +711,8 @@ __device__ __forceinline__ void view_ready(const RunView& v) {
                "s"(v.policy));
 }
 
-// Batched form, one launch per generation over every member's tiles (sorted by
+// Batched form, one launch per generation (where two are not taken at a time:
+// see below) over every member's tiles (sorted by
 // class, so neighbouring wavefronts run the same shape). Wavefront w runs the
 // tile in slot w of the table, which the host lays out so that each XCD's
 // workgroups (the dispatcher hands workgroup g to XCD g mod 8) take a
@@ -735,8 +737,15 @@ __global__ __launch_bounds__(1024) void batch_all_kernel(const RunView* __restri
     view_ready(v);                                           \
     const uint64_t t0 = const_u64(v.gen), left = const_u64(v.gen + 1); \
     asm volatile("" ::"s"(t0), "s"(left));                   \
-    if (left <= gen_offset) return;                          \
-    chunk_generation<L, S>(v, first, t0 + gen_offset, lds);  \
+    uint64_t ran = gen_offset;                               \
+    if (gen_offset >= kBatchSingle) {                        \
+      const uint32_t n = (gen_offset & ~kBatchSingle) >> 2, s = gen_offset & 3u; \
+      const uint64_t takes = left < n ? left : n;            \
+      ran = (takes & ~3ull) + s;                             \
+      if (ran >= takes) return;                              \
+    }                                                        \
+    if (left <= ran) return;                                 \
+    chunk_generation<L, S>(v, first, t0 + ran, lds);         \
     break;                                                   \
   }
     GA_BATCH_CASE(0, 1) GA_BATCH_CASE(0, 2) GA_BATCH_CASE(1, 1) GA_BATCH_CASE(1, 2)
@@ -746,6 +755,53 @@ __global__ __launch_bounds__(1024) void batch_all_kernel(const RunView* __restri
 #undef GA_BATCH_CASE
     default: break;  // an empty slot (members' classes are validated on admission)
   }
+}
+
+// Two generations of every member that has four or more left, from the
+// block's generation `ran` on (even): wavefront w again takes slot w, in a group
+// of its own as pair_kernel's do. Slots are laid out and members read as above.
+// What members have left over fours runs in batch_all_kernel at the block's end,
+// so that this kernel's registers (93, five wavefronts a SIMD) are not the
+// single body's too. 64 runs of 8 to 64 members: 30.4 us per generation, 42.3 one
+// at a time; 24 requests through 16 slots, where a generation is little work:
+// 22.9 ms against 51.9.
+__global__ __launch_bounds__(64) void batch_pair_kernel(const RunView* __restrict__ views,
+                                                        const Tile* __restrict__ tiles,
+                                                        uint32_t ran) {
+  const uint32_t run = const_word(&tiles[blockIdx.x].run);
+  const uint32_t first = const_word(&tiles[blockIdx.x].first);
+  switch (const_word(&tiles[blockIdx.x].cls)) {
+#define GA_BATCH_CASE(L, S)                                  \
+  case L * 2 + S - 1: {                                      \
+    const RunView v = load_member(views, run);               \
+    view_ready(v);                                           \
+    asm volatile("" ::"s"(v.cand), "s"(v.island_stride));    \
+    const uint64_t t0 = const_u64(v.gen), left = const_u64(v.gen + 1); \
+    asm volatile("" ::"s"(t0), "s"(left));                   \
+    if ((left & ~3ull) <= ran) return;                       \
+    const uint32_t plane = ((uint32_t)t0 ^ 1u ^ (ran >> 1)) & 1u; \
+    if (is_plain(v))                                         \
+      chunk_pair<L, S, FitnessModel, false, true>(v, first, t0 + ran, plane); \
+    else                                                     \
+      chunk_pair<L, S, FitnessModel, false, false>(v, first, t0 + ran, plane); \
+    break;                                                   \
+  }
+    GA_BATCH_CASE(2, 1) GA_BATCH_CASE(2, 2) GA_BATCH_CASE(3, 1) GA_BATCH_CASE(3, 2)
+    GA_BATCH_CASE(4, 1) GA_BATCH_CASE(4, 2) GA_BATCH_CASE(5, 1) GA_BATCH_CASE(5, 2)
+    GA_BATCH_CASE(6, 1) GA_BATCH_CASE(6, 2)
+#undef GA_BATCH_CASE
+    default: break;  // an empty slot (smaller islands keep a batch to single generations)
+  }
+}
+
+__global__ __launch_bounds__(64) void batch_candidate_kernel(const RunView* __restrict__ views,
+                                                             const Tile* __restrict__ tiles) {
+  const Tile tile = tiles[blockIdx.x];
+  if (tile.cls == kNoTile) return;
+  RunView v = views[tile.run];
+  from_table(v, views);
+  const uint32_t i = tile.first + threadIdx.x;
+  if (v.migration && threadIdx.x < v.ipw && i < v.islands) leave_candidate(v, i, *v.gen);
 }
 
 __global__ void store_u64_kernel(unsigned long long* p, unsigned long long value) {
@@ -770,10 +826,6 @@ __global__ void batch_advance_kernel(const RunView* views, const uint32_t* n_run
 size_t lds_bytes(uint32_t ipw, uint32_t waves, uint32_t model) {
   return (5u * ipw + 1u) * sizeof(uint4) * (model_has_string(model) ? 2u : 1u) * waves;
 }
-
-namespace {
-bool is_plain(const RunView& v) { return v.k == 2u && v.selection && !v.law; }
-}  // namespace
 
 hipError_t launch_generation(const RunView& v, uint32_t gen_offset, uint32_t waves,
                              uint32_t waves_per_group, hipStream_t stream) {
@@ -905,6 +957,16 @@ hipError_t launch_batch_all(const RunView* views, const Tile* tiles, uint32_t gr
                             hipStream_t stream) {
   if (grid_waves == 0) return hipSuccess;
   if (waves_per_group == 0 || grid_waves % waves_per_group) return hipErrorInvalidValue;
+  if (gen_offset >= kBatchCandidates) {
+    batch_candidate_kernel<<<dim3(grid_waves), dim3(64), 0, stream>>>(views, tiles);
+    return hipGetLastError();
+  }
+  if (gen_offset >= kBatchPair && gen_offset < kBatchSingle) {
+    // the largest class: 512 agents of four words
+    batch_pair_kernel<<<dim3(grid_waves), dim3(64), pair_bytes(5u, 4u), stream>>>(
+        views, tiles, gen_offset & ~kBatchPair);
+    return hipGetLastError();
+  }
   const uint32_t groups = grid_waves / waves_per_group;
   const size_t lds = lds_bytes(max_ipw, waves_per_group, 0u);
   batch_all_kernel<<<dim3(groups), dim3(64 * waves_per_group), lds, stream>>>(

@@ -70,6 +70,11 @@ __device__ __forceinline__ uint32_t entry_word(uint32_t k) {
   return STR && SW == 1 && k >= 3u ? k + 1u : k;
 }
 
+// A tournament of two under the discrete mutation law (what breed's PLAIN is).
+__host__ __device__ __forceinline__ bool is_plain(const RunView& v) {
+  return v.k == 2u && v.selection && !v.law;
+}
+
 // A lane's value handed to the other lanes of its group of four: lane FROM's.
 template <int FROM>
 __device__ __forceinline__ uint32_t from_quad(uint32_t x) {

@@ -2,12 +2,13 @@
 that straddle several rows, cover more than one pass of islands, end past the
 last island or come short of a wavefront's planes; every policy, string model
 and tournament size; from generations of every remainder by four, in one step,
-in captured blocks and over an outbox and a population set from outside."""
+in captured blocks and over an outbox and a population set from outside; and
+batches of them, whose members end at every remainder by four."""
 import pytest
 
 import oracle
 from gpu_helpers import assert_same_state, oracle_after, say
-from paper_2405_03605_amd import FORM_STREAMING, GARun
+from paper_2405_03605_amd import FORM_STREAMING, GABatch, GAPool, GARun
 from paper_2405_03605_amd.workloads import run_config
 
 pytestmark = pytest.mark.gpu
@@ -80,3 +81,74 @@ def test_pairs_from_a_state_set_from_outside():
     ref.step(30)
     assert_same_state(run.read(), ref, "pairs set back")
     run.close()
+
+
+MEMBERS = [
+    (run_config(width=5, height=3, pop=8, sites=32, k=3, run_id=81), 64),
+    (run_config(width=17, height=9, pop=16, sites=64, k=8, selection=0, run_id=82), 41),
+    (run_config(width=12, height=12, pop=32, sites=32, k=2, run_id=83), 22),
+    (run_config(width=3, height=40, pop=64, sites=64, k=5, run_id=84), 43),
+    (run_config(width=33, height=2, pop=4, sites=32, k=2, run_id=85), 3),
+    (run_config(width=1, height=1, pop=64, sites=32, k=2, run_id=86), 1),
+    (run_config(width=9, height=11, pop=32, sites=64, migration=0, run_id=87), 45),
+    (run_config(width=14, height=6, pop=16, sites=32, k=5, law=1, p32=1417339207,
+                p_ben32=12884901, run_id=88), 18),
+]
+
+
+@pytest.mark.parametrize("block,ipw", [(0, 0), (3, 0), (10, 0), (16, 16), (9, 64)])
+def test_batch_pairs_match_oracle(block, ipw):
+    say(f"batch of pairs, block {block}, ipw {ipw}")
+    runs = [GARun(c) for c, _ in MEMBERS]
+    batch = GABatch()
+    batch.set_graph_block(block)
+    if ipw:
+        batch.set_launch(ipw, 4)
+    for r, (_, budget) in zip(runs, MEMBERS):
+        batch.add(r, budget)
+    for n in (6, 21, 10, 30):
+        batch.step(n)
+    for r, (c, budget) in zip(runs, MEMBERS):
+        assert_same_state(r.read(), oracle_after(c, budget), f"member {c['run_id']}")
+    batch.close()
+
+
+def test_batch_changes_between_pairs_and_single_generations():
+    one = run_config(width=9, height=7, pop=2, sites=32, k=2, run_id=89)
+    cfg = MEMBERS[2][0]
+    say("a member of two agents an island joins and leaves a batch of pairs")
+    a, b = GARun(cfg), GARun(one)
+    batch = GABatch()
+    batch.set_graph_block(8)
+    batch.add(a, 1000)
+    batch.step(27)
+    batch.add(b, 1000)
+    batch.step(19)
+    batch.remove(b)
+    batch.step(38)
+    batch.remove(a)
+    batch.close()
+    a.set_launch(form=FORM_STREAMING)
+    a.step(5)
+    assert_same_state(a.read(), oracle_after(cfg, 89), "a")
+    assert_same_state(b.read(), oracle_after(one, 19), "b")
+
+
+def test_pool_runs_take_pairs():
+    say("pool of pairs, candidates in the batch's memory")
+    pool = GAPool(64 << 20, 8)
+    pool.set_graph_block(8)
+    tickets = {}
+    for c, budget in MEMBERS[:4]:
+        tickets[pool.admit(c, budget)] = (c, budget)
+    pool.step(20)
+    for c, budget in MEMBERS[4:]:
+        tickets[pool.admit(c, budget)] = (c, budget)
+    pool.step(13)
+    pool.step(47)
+    for t, (c, budget) in tickets.items():
+        assert pool.remaining(t) == 0
+        ids, T, D = pool.retire(t)[:3]
+        f, rT, rD = oracle_after(c, budget).population()
+        assert (T == rT[ids]).all() and (D == rD.reshape(len(rT), -1)[ids]).all()
+    pool.close()
