@@ -368,9 +368,16 @@ uint32_t waves_for(const ga_run* r, uint32_t ipw) {
 // LDS of one CU (gfx950), the most a workgroup can take.
 constexpr size_t kMaxGroupLds = 160 * 1024;
 
-// Default lower bound on a tile's agents: below it the per-generation
-// exchange between tiles costs more than the work it spreads.
-constexpr uint32_t kMinTileAgents = 2048;
+// The default tiling. A run of up to kOneTileAgents is one tile, which waits for
+// nobody (8 x 8 x 32: 1.69 us per generation; four tiles to sixteen would be at
+// 1.6). Larger ones take the smallest tiles of kMinTileAgents or more that leave
+// at most one per CU: the exchange costs about 0.5 us a generation however many
+// tiles there are, a wavefront's pass more than that (16 x 16 x 32 in tiles of 64,
+// 128, 256, 512, 1024, 2048 and 4096 agents: 1.60 1.56 1.65 1.73 2.07 2.32 2.84 us;
+// 37 x 23 x 16: 1.65 1.66 1.64 1.73 2.07 2.32 2.88), until CUs have two tiles
+// (64 x 64 x 32 in 256 tiles: 1.78, in 512: 1.84, in 2048: 2.95; 100 x 100 x 32
+// in 169: 2.35, in 1250: 2.58). Without such a tiling kMinDenseTileAgents holds.
+constexpr uint32_t kOneTileAgents = 2048, kMinTileAgents = 128, kMinDenseTileAgents = 2048;
 
 uint32_t ceil_div(uint32_t a, uint32_t b) { return (a + b - 1) / b; }
 
@@ -400,14 +407,17 @@ int tile_fits(const ga::RunView& v, const TileCand& c, uint32_t cus, bool* fits)
   return GA_OK;
 }
 
-// The tiling of the LDS-resident form: the caller's tile shape, or the one
-// that spreads the run over the most CUs (smallest tiles, but not below
-// kMinTileAgents agents), then the fewest tiles, then the squarest; every
-// tile's workgroup must be resident at once. Sets view.tile_* and tile_state.
+// The tiling of the LDS-resident form: the caller's tile shape, or of those with
+// at most one tile per CU (a small run: one tile) the one with the smallest
+// tiles, by the bounds above, then the shortest edges in all; every tile's
+// workgroup must be resident at once. Sets view.tile_* and tile_state.
 int plan_tiles(ga_run* r) {
   if (r->tile_state != 0) return GA_OK;
   ga::RunView& v = r->view;
   const uint32_t W = v.width, H = v.height, N = 1u << v.log2n;
+  int device = 0, cus = 0;
+  GA_HIP(hipGetDevice(&device), "get device");
+  GA_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device), "CU count");
   std::vector<TileCand> cands;
   if (r->want_tile_w) {
     cands.push_back(tile_cand(v, std::min(r->want_tile_w, W), std::min(r->want_tile_h, H)));
@@ -418,7 +428,7 @@ int plan_tiles(ga_run* r) {
       if (ws.empty() || ws.back() != ceil_div(W, k)) ws.push_back(ceil_div(W, k));
     for (uint32_t k = 1; k <= H; ++k)
       if (hs.empty() || hs.back() != ceil_div(H, k)) hs.push_back(ceil_div(H, k));
-    const uint64_t floor_agents = std::min<uint64_t>((uint64_t)v.agents, kMinTileAgents);
+    const bool one = v.agents <= kOneTileAgents;
     for (uint32_t tw : ws)
       for (uint32_t th : hs) {
         const TileCand c = tile_cand(v, tw, th);
@@ -426,16 +436,15 @@ int plan_tiles(ga_run* r) {
         cands.push_back(c);
       }
     auto key = [&](const TileCand& c) {
-      const uint64_t agents = (uint64_t)c.tw * c.th * N;
-      return std::make_tuple(std::max(agents, floor_agents), (uint64_t)c.gx * c.gy,
-                             c.tw + c.th, c.tw);
+      const uint64_t tiles = (uint64_t)c.gx * c.gy;
+      const bool dense = one ? tiles > 1 : tiles > (uint64_t)cus;
+      const uint64_t agents = std::max<uint64_t>((uint64_t)c.tw * c.th * N,
+                                                 dense ? kMinDenseTileAgents : kMinTileAgents);
+      return std::make_tuple(dense, agents, tiles * (c.tw + c.th), c.tw);
     };
     std::sort(cands.begin(), cands.end(),
               [&](const TileCand& a, const TileCand& b) { return key(a) < key(b); });
   }
-  int device = 0, cus = 0;
-  GA_HIP(hipGetDevice(&device), "get device");
-  GA_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device), "CU count");
   for (const TileCand& c : cands) {
     bool fits = false;
     const int rc = tile_fits(v, c, (uint32_t)cus, &fits);

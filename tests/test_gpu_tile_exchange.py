@@ -78,3 +78,26 @@ def test_set_back_to_an_earlier_generation():
     assert_same_state(run.read(), ref, "set back")
     run.close()
     assert np.isfinite(snap["f"]).all()
+
+
+@pytest.mark.parametrize("edge", [
+    dict(width=8, height=8, pop=32, k=2, seed=51),          # 2,048 agents: one tile
+    dict(width=13, height=5, pop=32, k=2, seed=52),         # the first size past it
+    dict(width=41, height=50, pop=1, k=1, seed=53),
+    dict(width=1000, height=3, pop=16, sites=64, k=4, model=2, policy=2, seed=54),
+    dict(width=67, height=61, pop=16, k=2, seed=55),        # just under one tile per CU
+    dict(width=211, height=97, pop=2, k=2, seed=56),
+], ids=lambda e: "-".join(f"{k}{v}" for k, v in e.items()))
+def test_default_tilings_match_oracle(edge):
+    import torch
+    cfg = run_config(**edge)
+    run = GARun(cfg)
+    tw, th, n = run.tiles()
+    say(f"default tiling {tw} x {th}, {n} tiles, of {cfg}")
+    agents = edge["width"] * edge["height"] * edge["pop"]
+    assert (n == 1) == (agents <= 2048)
+    assert n <= torch.cuda.get_device_properties(0).multi_processor_count
+    for steps in (1, 8, 31):
+        run.step(steps)
+    assert_same_state(run.read(), oracle_after(cfg, 40), f"tiling {edge}")
+    run.close()
