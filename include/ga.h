@@ -161,7 +161,10 @@ typedef struct ga_config {
  * There is no barrier across the grid: wavefronts of one persistent launch
  * each own a range of islands and run the generations, an island waiting only
  * while a neighbour is more than a set number of generations behind (see
- * ga_set_async). Every random draw is the same as in the synchronous schedule;
+ * ga_set_async). Calls of 48 generations and more at the default pacing, whose
+ * results are the synchronous schedule's, run their inner generations in the
+ * streaming form instead (ga_init allocates 64 bytes an island for it, 128 with
+ * 64 sites or a genome string) and leave the buffers as the launch would. Every random draw is the same as in the synchronous schedule;
  * only the moment a genome is read differs. With the default pacing, or
  * migration off, the results equal the synchronous schedule's unless a wait
  * gave up; looser pacing lets genomes arrive late or be overwritten unread,
@@ -290,9 +293,10 @@ int ga_set_launch(ga_run* run, uint32_t islands_per_wave, uint32_t waves_per_gro
                   uint32_t form);
 
 /* Tile shape of the resident form: tile_w x tile_h islands (clamped to the
- * torus), or 0, 0 to let the library choose (the default: the smallest tiles,
- * but not under 2,048 agents, whose workgroups all fit the GPU at once; then
- * the fewest and squarest). GA_EINVAL for an asynchronous run, for one side
+ * torus), or 0, 0 to let the library choose (the default: one tile for up to
+ * 2,048 agents, else the smallest tiles of 128 agents or more of which there is
+ * at most one per CU, where such fit, else the smallest of 2,048 or more whose
+ * workgroups all fit the GPU at once; then the shortest edges in all). GA_EINVAL for an asynchronous run, for one side
  * given without the other, or if the tiles do not fit (LDS of a CU, or more
  * workgroups than the GPU holds at once); the run then keeps its tiling.
  * Results do not depend on the tile shape. */
@@ -304,7 +308,8 @@ int ga_get_tiles(ga_run* run, uint32_t* tile_w, uint32_t* tile_h, uint32_t* tile
 /* Asynchronous runs only (GA_EINVAL for a synchronous run).
  *
  * max_wavefronts caps the wavefronts of a launch (0, the default: as many as
- * the GPU holds at once, from the occupancy of the kernel).
+ * the GPU holds at once, from the occupancy of the kernel); with a cap every
+ * launch is the persistent one.
  *
  * max_lead bounds how many generations an island may run ahead of a
  * neighbour: before generation t an island waits until each neighbour has

@@ -213,7 +213,10 @@ struct ga_run {
   Layout lay{};
   hipStream_t stream = nullptr;
   uint8_t* base = nullptr;
-  void* own = nullptr;  // view.cand and view.exchange
+  void* own = nullptr;  // view.cand and view.exchange, or async_ob
+  // asynchronous runs: two candidate planes, then two outbox planes for the
+  // streaming form (NULL: none)
+  uint32_t* async_ob = nullptr;
   uint64_t gen_host = 0;
   uint32_t ipw = 64;
   bool ipw_set = false;  // islands per wavefront chosen by the caller (not the default)
@@ -523,21 +526,20 @@ void drop_graph(ga_run* r) {
 // two generations a launch as far as fours go (two such launches bring the
 // outbox back to the plane the single one reads), the candidates they start
 // from taken from the population first, so nothing is kept from an earlier call.
-hipError_t launch_streaming(const ga_run* r, uint32_t n, hipStream_t s) {
-  ga::RunView v = r->view;
+hipError_t launch_streaming(const ga_run* r, ga::RunView v, uint32_t n, hipStream_t s) {
   const bool pairs = v.log2n >= ga::kPairMinLog && (v.cand || !v.migration);
   const uint32_t fours = pairs ? n & ~3u : 0u;
   hipError_t e = hipSuccess;
   if (fours) {
     v.ipw = r->ipw;
     v.ipw = pair_ipw(v);
-    v.span = 0u;
+    v.span = ga::kSpanCandidates;
     if (v.migration) e = ga::launch_generation(v, 0u, 1u, 1u, s);
-    v.span = 2u;
+    v.span = ga::kSpanTwo;
     for (uint32_t g = 0; g < fours && e == hipSuccess; g += 2u)
       e = ga::launch_generation(v, g, waves_for(r, v.ipw), 1u, s);
   }
-  v.span = 1u;
+  v.span = ga::kSpanOne;
   v.ipw = r->ipw;
   for (uint32_t g = fours; g < n && e == hipSuccess; ++g)
     e = ga::launch_generation(v, g, waves_for(r, v.ipw), r->wpg, s);
@@ -548,7 +550,7 @@ int enqueue_direct(ga_run* r, uint64_t n) {
   // in slices whose generation offsets fit a 32-bit argument
   while (n > 0) {
     const uint64_t slice = std::min<uint64_t>(n, 1u << 20);
-    GA_HIP(launch_streaming(r, (uint32_t)slice, r->stream), "generation launch");
+    GA_HIP(launch_streaming(r, r->view, (uint32_t)slice, r->stream), "generation launch");
     n -= slice;
   }
   return GA_OK;
@@ -562,7 +564,7 @@ int ensure_graph(ga_run* r) {
   if (!r->capture_stream)
     GA_HIP(hipStreamCreateWithFlags(&r->capture_stream, hipStreamNonBlocking), "capture stream");
   GA_HIP(hipStreamBeginCapture(r->capture_stream, hipStreamCaptureModeThreadLocal), "begin capture");
-  hipError_t err = launch_streaming(r, r->graph_block, r->capture_stream);
+  hipError_t err = launch_streaming(r, r->view, r->graph_block, r->capture_stream);
   hipGraph_t graph = nullptr;
   hipError_t end = hipStreamEndCapture(r->capture_stream, &graph);
   if (err != hipSuccess) {
@@ -581,10 +583,60 @@ int ensure_graph(ga_run* r) {
   return GA_OK;
 }
 
+// The lockstep exchange (default pacing, no cap on the wavefronts) over n > 2
+// generations. Its results are the synchronous schedule's, so only the first
+// generation, which takes what an earlier launch left under the general rule, and
+// the last, which leaves the mail as any other launch expects it, run on the
+// mail; those between run in the streaming form, without waits, and what they
+// would have recorded is worked out at their end. The persistent launch, which
+// waits for each neighbour's headers and reads every genome from HBM each
+// generation, takes 25 us per generation at 512 x 256 x 32 and 123 at 1024 x 512 x
+// 32; this takes 12.5 and 36 between its ends, which cost as much as about 20
+// generations of it: at 32 generations in a call the two are even from
+// 8 x 8 x 32 (106 against 116 us) to 512 x 256 x 32 (698 against 766), with
+// 100 x 100 x 32 the furthest behind (265 against 233), at 400 it is ahead by
+// 1.5 to 3.1. A run with a cap on its wavefronts, or with fewer generations in
+// the call, keeps the persistent launch.
+constexpr uint64_t kLockstepLeast = 48;
+
+int step_lockstep(ga_run* r, uint64_t n) {
+  ga::RunView v = r->view;
+  v.ipw = r->ipw;
+  ga::RunView between = v;
+  between.cand = r->async_ob;
+  const size_t plane = cand_bytes(v) / 8;  // words
+  for (int p = 0; p < 2; ++p) between.ob[p] = r->async_ob + (size_t)(2 + p) * plane;
+  // no wait in a launch of one generation: the prologue has written every
+  // header that it looks at, so all chunks may be launched at once
+  auto one = [&]() -> int {
+    GA_HIP(ga::launch_lockstep(v, r->gen_host, 1, waves_for(r, v.ipw), 1, r->wpg, r->stream),
+           "lockstep launch");
+    GA_HIP(ga::launch_advance(v.gen, 1, r->stream), "advance launch");
+    r->gen_host += 1;
+    return GA_OK;
+  };
+  int rc = one();
+  if (rc != GA_OK) return rc;
+  between.span = ga::kSpanFromMail;
+  GA_HIP(ga::launch_generation(between, 0, 1, 1, r->stream), "outbox launch");
+  for (uint64_t left = n - 2; left > 0;) {
+    const uint64_t slice = std::min<uint64_t>(left, 1u << 20);
+    GA_HIP(launch_streaming(r, between, (uint32_t)slice, r->stream), "generation launch");
+    between.span = ga::kSpanToMail;
+    GA_HIP(ga::launch_generation(between, (uint32_t)slice, 1, 1, r->stream), "mail launch");
+    r->gen_host += slice;
+    left -= slice;
+  }
+  return one();
+}
+
 // Asynchronous schedule: one persistent launch per slice of generations, the
 // chunks spread over as many wavefronts as the GPU holds at once (or over the
 // caller's cap), each wavefront owning consecutive chunks.
 int step_async(ga_run* r, uint64_t n) {
+  if (n >= kLockstepLeast && r->async_lead == 0u && r->async_skew == 0u &&
+      r->async_max_waves == 0u && r->async_ob && r->view.log2n >= ga::kPairMinLog)
+    return step_lockstep(r, n);
   ga::RunView v = r->view;
   v.ipw = r->ipw;
   // no lead and no skew: the lockstep exchange
@@ -662,7 +714,7 @@ namespace {
 
 // What a run that may be stepped by itself has beside the caller's memory: the
 // candidates of the streaming form, and the exchange area of the LDS-resident one
-// where the population could fit the GPU's LDS. One small allocation of the
+// where the population could fit the GPU's LDS, or an asynchronous run's outbox. One small allocation of the
 // library's own; without it (no memory left) the forms run one generation per
 // launch. Made here, not on the first step, so that a step can be captured.
 void alloc_own(ga_run* r) {
@@ -675,14 +727,20 @@ void alloc_own(ga_run* r) {
   const size_t agent_bytes = 4 * (size_t)(2 + v.words + (strings ? 2 : 0));
   const size_t cand = cand_bytes(v);
   const bool resident = v.agents * agent_bytes <= (size_t)cus * kMaxGroupLds;
-  const size_t exchange =
-      resident ? 2 * (size_t)v.islands * ga::exchange_words(strings) * 8 : 0;
+  const bool async = r->cfg.schedule == GA_SCHEDULE_ASYNC;
+  const size_t exchange = async      ? cand
+                          : resident ? 2 * (size_t)v.islands * ga::exchange_words(strings) * 8
+                                     : 0;
   void* p = nullptr;
   if (hipMalloc(&p, cand + exchange) != hipSuccess) {
     (void)hipGetLastError();
     return;
   }
   r->own = p;
+  if (async) {
+    r->async_ob = static_cast<uint32_t*>(p);
+    return;
+  }
   v.cand = static_cast<uint32_t*>(p);
   if (resident)
     v.exchange = reinterpret_cast<unsigned long long*>(static_cast<uint8_t*>(p) + cand);
@@ -760,7 +818,7 @@ int init_run(const ga_config* cfg, void* dev_mem, size_t bytes, void* hip_stream
   // outbox headers, generation 0.
   hipError_t e = ga::launch_fill(reinterpret_cast<uint32_t*>(b), 0u, lay.total / 4, r->stream);
   if (e == hipSuccess) e = ga::launch_init(v, r->stream);
-  if (e == hipSuccess && alone && !async && v.migration) {
+  if (e == hipSuccess && alone && v.migration) {
     alloc_own(r);
     e = clear_exchange(v, 0, r->stream);
   }

@@ -73,10 +73,16 @@ struct RunView {
   // generation t in cand[((t >> 1 & 1) * island_stride + i) * ob_stride + k], k as
   // in an outbox entry (no header); NULL without them
   uint32_t* cand;
-  // what a streaming launch does: 1 one generation, 2 two, 0 nothing but leave
-  // the candidates of the generation it is given
+  // what a streaming launch does (kSpan*)
   uint32_t span;
 };
+
+// A streaming launch at generation t runs one generation or two, or leaves the
+// candidates of t. An asynchronous run in lockstep passes through the streaming
+// form (its outbox planes then in ob): its genomes of t - 1 go from its mail to
+// the outbox before, and back after (kSpanToMail: see mail_kernel).
+constexpr uint32_t kSpanCandidates = 0, kSpanOne = 1, kSpanTwo = 2, kSpanFromMail = 3,
+                   kSpanToMail = 4;
 
 // Streaming launches of two generations: a wavefront's chunk is 16 islands, four
 // lanes to each, but at most 512 agents, in LDS planes of one word per agent with

@@ -624,6 +624,54 @@ __global__ void lockstep_prologue_kernel(RunView v, uint32_t t0) {
   *lock_header(v.lock, j, d, p, v.island_stride) = (e0 || e1) ? due : due + 1u;
 }
 
+// The genomes of t - 1 of an asynchronous run whose islands all sent one (a
+// lockstep generation behind it), from the mail to the outbox plane the streaming
+// form reads at t. A buffer without that stamp sent nothing.
+__global__ void outbox_kernel(RunView v) {
+  const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= v.islands) return;
+  const uint64_t g = *v.gen - 1u;
+  const Block b = philox10(0u, i, (uint32_t)g, ((uint32_t)(g >> 32) << 2) | kStreamMigrate, v.seed,
+                           v.run_id);
+  const uint32_t d = b.y >> 30, p = (uint32_t)g & 1u;
+  const uint32_t ob_hdr = model_has_string(v.model) ? 6u : 2u + v.words;
+  const uint32_t* from = mail_entry(v.mail, i, d, p, v.ob_stride);
+  uint32_t* to = v.ob[p] + (size_t)i * v.ob_stride;
+  for (uint32_t k = 0; k < ob_hdr; ++k) to[k] = from[k];
+  to[ob_hdr] = from[ob_hdr] == 2u * ((uint32_t)g + 1u) ? kMetaValid | d : 0u;
+}
+
+// Back: the genomes of t - 1 into the mail with their stamps, for the general
+// rule to take, and what the `ran` generations before t would have recorded as
+// lockstep ones: island i's genome of generation g, t - 1 - ran <= g < t - 1, was
+// taken by the neighbour it was sent to, so the last one sent each way in that
+// time is that neighbour's newest (the draws tell which: about eight of them
+// until every way has come up), and as many were taken as were sent.
+__global__ void mail_kernel(RunView v, uint32_t ran) {
+  const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i == 0u) v.waits[1] += (unsigned long long)v.islands * ran;
+  if (i >= v.islands) return;
+  const uint64_t t = *v.gen;
+  const uint32_t p = (uint32_t)(t - 1u) & 1u;
+  const uint32_t ob_hdr = model_has_string(v.model) ? 6u : 2u + v.words;
+  const uint32_t* from = v.ob[p] + (size_t)i * v.ob_stride;
+  uint32_t* to = mail_entry(v.mail, i, from[ob_hdr] & 3u, p, v.ob_stride);
+  for (uint32_t k = 0; k < ob_hdr; ++k) to[k] = from[k];
+  to[ob_hdr] = 2u * (uint32_t)t;
+  const uint32_t x = i % v.width, y = i / v.width;
+  uint32_t open = 15u;
+  for (uint32_t back = 2; back <= ran + 1u && open; ++back) {
+    const uint64_t g = t - back;
+    const Block b = philox10(0u, i, (uint32_t)g, ((uint32_t)(g >> 32) << 2) | kStreamMigrate,
+                             v.seed, v.run_id);
+    const uint32_t d = b.y >> 30;
+    if (open & (1u << d))
+      v.seen[(size_t)torus_step(x, y, d, v.width, v.height) * 4u + (d ^ 2u)] =
+          2u * ((uint32_t)g + 1u);
+    open &= ~(1u << d);
+  }
+}
+
 __global__ void advance_kernel(unsigned long long* gen, uint64_t n) {
   if (blockIdx.x == 0 && threadIdx.x == 0) *gen = *gen + n;
 }
@@ -832,11 +880,19 @@ hipError_t launch_generation(const RunView& v, uint32_t gen_offset, uint32_t wav
   if (waves == 0) return hipSuccess;
   const uint32_t groups = (waves + waves_per_group - 1) / waves_per_group;
   const dim3 grid(groups), block(64 * waves_per_group);
-  if (v.span == 0u) {
-    candidate_kernel<<<dim3((v.islands + 255u) / 256u), dim3(256), 0, stream>>>(v, gen_offset);
-    return hipGetLastError();
+  const dim3 islands((v.islands + 255u) / 256u);
+  switch (v.span) {
+    case kSpanCandidates:
+      candidate_kernel<<<islands, dim3(256), 0, stream>>>(v, gen_offset);
+      return hipGetLastError();
+    case kSpanFromMail:
+      outbox_kernel<<<islands, dim3(256), 0, stream>>>(v);
+      return hipGetLastError();
+    case kSpanToMail:
+      mail_kernel<<<islands, dim3(256), 0, stream>>>(v, gen_offset);
+      return hipGetLastError();
   }
-  if (v.span == 2u)
+  if (v.span == kSpanTwo)
     return dispatch(v, [&](auto LC, auto SWC, auto M, auto WD) {
       constexpr uint32_t L = decltype(LC)::value;
       constexpr uint32_t kw = pair_words(decltype(SWC)::value, decltype(M)::kString);
