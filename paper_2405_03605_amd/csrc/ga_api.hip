@@ -359,7 +359,8 @@ uint32_t default_ipw(const ga::RunView& v) {
 // Of a chunk of v.ipw islands what a launch of two generations takes (in whole
 // iterations), and the bytes of a run's candidates.
 uint32_t pair_ipw(const ga::RunView& v) {
-  const uint32_t ipw = std::min(v.ipw, ga::pair_agents(v.log2n) >> v.log2n);
+  const uint32_t kw = ga::pair_words(v.words, ga::model_has_string_host(v.model));
+  const uint32_t ipw = std::min(v.ipw, ga::pair_agents(v.log2n, kw) >> v.log2n);
   return ipw - ipw % (64u >> v.log2n);
 }
 size_t cand_bytes(const ga::RunView& v) { return 2 * (size_t)v.island_stride * v.ob_stride * 4; }

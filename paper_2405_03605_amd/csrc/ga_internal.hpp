@@ -86,17 +86,25 @@ constexpr uint32_t kSpanCandidates = 0, kSpanOne = 1, kSpanTwo = 2, kSpanFromMai
 
 // Streaming launches of two generations: a wavefront's chunk is 16 islands, four
 // lanes to each, but at most 512 agents, in LDS planes of one word per agent with
-// a 64-bit product per island behind them. Chunks are whole iterations of 64
+// a 64-bit product per island behind them. From four words per agent on it is at
+// most 256, so that a CU's LDS holds 20 and more wavefronts: 512 would leave it
+// 19 (four words) or 12 (six), and cost 300 x 200 x 64 trap-4 23.8 us per
+// generation against 18.6, 512 x 256 x 32 with 64 sites 16.6 against 14.8 (but
+// 1024 x 512 x 32, k = 3, past the last-level cache: 57.7 against 60.7). Chunks are whole iterations of 64
 // agents, so islands of fewer than four (64 / N > 16) have no such launch.
 constexpr uint32_t kPairMinLog = 2;
 constexpr uint32_t pair_words(uint32_t words, bool strings) {
   return 2u + words + (strings ? 2u : 0u);
 }
-constexpr uint32_t pair_agents(uint32_t log2n) { return log2n < 5u ? 16u << log2n : 512u; }
-constexpr uint32_t pair_plane(uint32_t log2n) {
-  return log2n < 4u ? 1024u : 4u * pair_agents(log2n);
+constexpr uint32_t pair_agents(uint32_t log2n, uint32_t kw) {
+  return kw > 3u ? (log2n < 4u ? 16u << log2n : 256u) : (log2n < 5u ? 16u << log2n : 512u);
 }
-constexpr uint32_t pair_bytes(uint32_t log2n, uint32_t kw) { return kw * pair_plane(log2n) + 256u; }
+constexpr uint32_t pair_plane(uint32_t log2n, uint32_t kw) {
+  return log2n < 4u ? 1024u : 4u * pair_agents(log2n, kw);
+}
+constexpr uint32_t pair_bytes(uint32_t log2n, uint32_t kw) {
+  return kw * pair_plane(log2n, kw) + 256u;
+}
 
 // 64-bit words of an exchange slot, and what an empty slot's halves hold while
 // the run is at generation t: no generation a launch from t on waits for.

@@ -1018,8 +1018,10 @@ hipError_t launch_batch_all(const RunView* views, const Tile* tiles, uint32_t gr
     return hipGetLastError();
   }
   if (gen_offset >= kBatchPair && gen_offset < kBatchSingle) {
-    // the largest class: 512 agents of four words
-    batch_pair_kernel<<<dim3(grid_waves), dim3(64), pair_bytes(5u, 4u), stream>>>(
+    // the largest class: 512 agents of three words, 256 of four
+    constexpr uint32_t lds = pair_bytes(6u, 3u) > pair_bytes(6u, 4u) ? pair_bytes(6u, 3u)
+                                                                    : pair_bytes(6u, 4u);
+    batch_pair_kernel<<<dim3(grid_waves), dim3(64), lds, stream>>>(
         views, tiles, gen_offset & ~kBatchPair);
     return hipGetLastError();
   }

@@ -107,7 +107,7 @@ __device__ __forceinline__ void chunk_pair(const RunView& v, uint32_t base, uint
   constexpr uint32_t SW = (uint32_t)SWC;
   constexpr bool kStr = Model::kString;
   constexpr uint32_t kw = pair_words(SW, kStr);
-  constexpr uint32_t kAgents = pair_agents(L), kPlane = pair_plane(L);
+  constexpr uint32_t kAgents = pair_agents(L, kw), kPlane = pair_plane(L, kw);
   constexpr uint32_t obs = (SW == 1 && !kStr) ? 4u : 8u;
   constexpr uint32_t ob_hdr = kStr ? 6u : 2u + SW;
   const uint32_t lane = __lane_id(), q = lane & 3u, li = lane >> 2;
