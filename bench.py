@@ -33,20 +33,20 @@ PEAK_HBM_GBPS = 8000.0          # MI355X HBM3E
 CUS, LANES_PER_CU, CLOCK_HZ = 256, 64, 2.4e9
 PEAK_LANE_OPS = CUS * LANES_PER_CU * CLOCK_HZ   # full-rate 32-bit VALU lane-ops/s
 PROFILES = os.path.join(ROOT, "profiles")
-COUNTER_FILES = {"paper-streaming": os.path.join(PROFILES, "counters_generation_kernel_paper.json"),
+COUNTER_FILES = {"paper-streaming": os.path.join(PROFILES, "counters_pair_kernel_paper.json"),
                  "mid-tiles": os.path.join(PROFILES, "counters_tile_kernel_mid.json"),
-                 "batch": os.path.join(PROFILES, "counters_batch_all_kernel_64runs.json")}
+                 "batch": os.path.join(PROFILES, "counters_batch_pair_kernel_64runs.json")}
 
 
 def algorithmic_bytes_per_generation(cfg: dict) -> int:
-    """HBM bytes one generation of the streaming form must move: every agent's
-    genome read and written once (fitness, T, S/32 surface words), and per
-    island one outbox entry written and one read (header, fitness, T, surface
-    words)."""
+    """HBM bytes one generation of the streaming form must move, half of what a
+    launch of two does: every agent's genome read and written once (fitness, T,
+    S/32 surface words), and per island one outbox entry and one candidate
+    (header or draw, fitness, T, surface words), each read and written once."""
     I = cfg["width"] * cfg["height"]
     A = I * cfg["pop"]
     genome = 8 + cfg["sites"] // 8
-    return 2 * genome * A + 2 * (4 + genome) * I
+    return genome * A + 2 * (4 + genome) * I
 
 
 def algorithmic_lane_ops_per_agent_generation(cfg: dict) -> float:
@@ -142,8 +142,8 @@ def roofline_streaming(cfg, us_per_gen, counters):
             "unit": "GB/s", "frac": round(achieved / PEAK_HBM_GBPS, 4),
             "traffic": counters["bytes_per_generation"] if counters else None,
             "valu_issue_frac": counters["valu_issue_frac"] if counters else None,
-            "kernel": "generation_kernel<5,1,FitnessModel,false>", "bytes_per_launch": bytes_gen,
-            "launch_us": round(us_per_gen, 2)}
+            "kernel": "pair_kernel<true,5,1,FitnessModel,false>",
+            "bytes_per_launch": 2 * bytes_gen, "launch_us": round(2 * us_per_gen, 2)}
 
 
 def roofline_tiles(cfg, us_per_gen, counters, tiles):
@@ -155,7 +155,7 @@ def roofline_tiles(cfg, us_per_gen, counters, tiles):
             "unit": "T lane-op/s", "frac": round(achieved / peak, 4),
             "traffic": counters["bytes_per_generation"] if counters else None,
             "valu_issue_frac": counters["valu_issue_frac"] if counters else None,
-            "kernel": "tile_kernel<5,1,FitnessModel,false>",
+            "kernel": "tile_kernel<false,5,1,FitnessModel,false>",
             "lane_ops_per_agent_generation": round(ops, 2),
             "tiles": {"tile_w": tiles[0], "tile_h": tiles[1], "count": tiles[2]},
             "us_per_generation": round(us_per_gen, 2)}
@@ -211,7 +211,7 @@ def bench_batched(gens: int, torch, tune: bool = True):
     plain = time.perf_counter() - t0
     for r in runs:
         r.close()
-    # batched: one launch per generation over every member's islands in
+    # batched: launches of two generations over every member's islands in
     # 100-generation graph blocks, launch shape chosen by the autotuner (timed
     # on scratch runs of the same shapes before the timed region)
     from paper_2405_03605_amd.autotune import autotune_batch
@@ -250,7 +250,7 @@ def bench_batched(gens: int, torch, tune: bool = True):
                          "bytes_per_generation": bytes_gen,
                          "traffic": counters["bytes_per_generation"] if counters else None,
                          "valu_issue_frac": counters["valu_issue_frac"] if counters else None,
-                         "kernel": "batch_all_kernel"}}
+                         "kernel": "batch_pair_kernel"}}
 
 
 def shape_names(chosen: dict) -> dict:

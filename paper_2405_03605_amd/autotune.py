@@ -164,9 +164,9 @@ def autotune_batch(batch: GABatch, cfgs: list, gens: int = 300, use_cache: bool 
     """Choose and apply the launch shape of a batch of runs with configurations
     cfgs: the batch-wide wavefronts per workgroup, then each class's islands
     per wavefront with the others held (coordinate descent), every candidate
-    timed (best of two) on a scratch batch of the same shapes in one launch
-    per generation, as the batch runs, and taken only if it beats the shape in
-    place by BATCH_MARGIN. Returns {"waves_per_group": w, (log2 N, words): ipw}."""
+    timed (best of two) on a scratch batch of the same shapes in the launches
+    the batch runs, and taken only if it beats the shape in place by
+    BATCH_MARGIN. Returns {"waves_per_group": w, (log2 N, words): ipw}."""
     import torch
     key = _batch_key(cfgs)
     if not (use_cache and key in _batch_cache):

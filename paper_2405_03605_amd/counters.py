@@ -6,9 +6,9 @@ command, run as a child process (this process never touches the GPU). The
 scale factors come from the library's in-place update roof kernel, whose
 bytes are exact.
 
-  python -m paper_2405_03605_amd.counters paper-streaming --out profiles/counters_generation_kernel_paper.json
+  python -m paper_2405_03605_amd.counters paper-streaming --out profiles/counters_pair_kernel_paper.json
   python -m paper_2405_03605_amd.counters mid-tiles --out profiles/counters_tile_kernel_mid.json
-  python -m paper_2405_03605_amd.counters batch --out profiles/counters_batch_all_kernel_64runs.json
+  python -m paper_2405_03605_amd.counters batch --out profiles/counters_batch_pair_kernel_64runs.json
   python -m paper_2405_03605_amd.counters batch-classes --out profiles/counters_batch_classes.json
 
 The record holds the sha256 of the kernel's sources; bench.py reports its
@@ -37,19 +37,20 @@ CSRC = os.path.join(HERE, "csrc")
 COMMON = ["ga_device.hpp", "ga_internal.hpp", "models/models.hpp", "models/fitness.hpp",
           "models/strings.hpp", "models/onemax.hpp", "models/trap4.hpp"]
 KERNELS = {
-    "paper-streaming": {"kernel": "generation_kernel", "sources": ["ga_kernels.hip"] + COMMON,
-                        "name": "generation_kernel<5,1,FitnessModel,false>",
+    "paper-streaming": {"kernel": "::pair_kernel<",
+                        "sources": ["ga_kernels.hip", "ga_pair.hpp"] + COMMON,
+                        "name": "pair_kernel<true,5,1,FitnessModel,false>",
                         "workload": "1024x512 islands x 32 agents, 32-site surface, tournament 2",
-                        "gens_per_dispatch": 1},
+                        "gens_per_dispatch": 2},
     "mid-tiles": {"kernel": "tile_kernel", "sources": ["ga_tile.hip"] + COMMON,
-                  "name": "tile_kernel<5,1,FitnessModel,false>",
+                  "name": "tile_kernel<false,5,1,FitnessModel,false>",
                   "workload": "256x256 islands x 32 agents, 32-site surface, tournament 2, "
                               "the autotuner's tiling (one tile per CU)",
                   "gens_per_dispatch": 200, "autotuned_tiles": True},
-    "batch": {"kernel": "batch_all_kernel", "sources": ["ga_kernels.hip"] + COMMON,
-              "name": "batch_all_kernel",
-              "workload": "64 uneven runs, 8,597,368 agents, one launch per generation",
-              "gens_per_dispatch": 1},
+    "batch": {"kernel": "batch_pair_kernel", "sources": ["ga_kernels.hip", "ga_pair.hpp"] + COMMON,
+              "name": "batch_pair_kernel",
+              "workload": "64 uneven runs, 8,597,368 agents, two generations per launch",
+              "gens_per_dispatch": 2},
 }
 SQ_SET = ["SQ_WAVES", "SQ_INSTS_VALU", "SQ_INSTS_SALU", "SQ_INSTS_LDS", "SQ_ACTIVE_INST_VALU",
           "SQ_BUSY_CYCLES", "SQ_WAVE_CYCLES", "SQ_INSTS_VALU_INT64", "GRBM_GUI_ACTIVE"]
@@ -187,7 +188,7 @@ def collect_classes(gens: int = 12) -> dict:
             with open(path) as fh:
                 for row in csv.DictReader(fh):
                     name = row.get("Kernel_Name", "")
-                    if "generation_kernel" not in name and "batch_all_kernel" not in name:
+                    if "::pair_kernel<" not in name and "batch_pair_kernel" not in name:
                         continue
                     d = per.setdefault(int(row["Dispatch_Id"]), {"kernel": name})
                     c = row["Counter_Name"]
@@ -195,14 +196,15 @@ def collect_classes(gens: int = 12) -> dict:
     finally:
         shutil.rmtree(tmp, ignore_errors=True)
     seq = [per[k] for k in sorted(per)]
-    if len(seq) != 2 * gens * len(CLASS_RUNS):
-        raise RuntimeError(f"expected {2 * gens * len(CLASS_RUNS)} dispatches, got {len(seq)}")
+    n = gens // 2    # dispatches of two generations
+    if len(seq) != 2 * n * len(CLASS_RUNS):
+        raise RuntimeError(f"expected {2 * n * len(CLASS_RUNS)} dispatches, got {len(seq)}")
     rows = []
     for i, (l, w) in enumerate(CLASS_RUNS):
-        plain = seq[2 * gens * i: 2 * gens * i + gens]
-        batch = seq[2 * gens * i + gens: 2 * gens * (i + 1)]
-        assert all("generation_kernel" in d["kernel"] for d in plain)
-        assert all("batch_all_kernel" in d["kernel"] for d in batch)
+        plain = seq[2 * n * i: 2 * n * i + n]
+        batch = seq[2 * n * i + n: 2 * n * (i + 1)]
+        assert all("::pair_kernel<" in d["kernel"] for d in plain)
+        assert all("batch_pair_kernel" in d["kernel"] for d in batch)
         cfg = class_config(l, w)
         row = {"N": 1 << l, "surface_words": w,
                "run": f"{cfg['width']}x{cfg['height']}x{cfg['pop']}, S={cfg['sites']}",
@@ -213,7 +215,7 @@ def collect_classes(gens: int = 12) -> dict:
         row["valu_ratio"] = round(row["batch_SQ_INSTS_VALU"] / row["plain_SQ_INSTS_VALU"], 4)
         row["salu_ratio"] = round(row["batch_SQ_INSTS_SALU"] / row["plain_SQ_INSTS_SALU"], 4)
         rows.append(row)
-    return {"kernel": "batch_all_kernel", "mode": "batch-classes",
+    return {"kernel": "batch_pair_kernel", "mode": "batch-classes",
             "kernel_source_sha256": source_hash("batch"), "generations_per_class": gens,
             "classes": rows,
             "commands": {"workload": " ".join(["python3"] + cmd[1:]),

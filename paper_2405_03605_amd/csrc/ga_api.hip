@@ -194,7 +194,7 @@ Layout layout_of(const ga_config* c) {
     L.lock = take(islands * 8 * 4);
   } else {
     for (int p = 0; p < 2; ++p) L.ob[p] = take(islands * 4 * outbox_stride(c));
-    // LDS-resident tiles: a progress word per tile (never more tiles than islands)
+    // a word per tile that the LDS-resident form once kept; part of the state's size
     L.prog = take(std::min<size_t>(kMaxTiles, (size_t)c->width * c->height) * 4);
   }
   L.counters = take(32);  // generation, batch budget, async give-ups, async genomes taken

@@ -1,7 +1,8 @@
 // Two generations of the streaming form in one launch, the population through
 // HBM once for both.
 //
-// A wavefront takes a chunk of 16 islands (at most 512 agents) into LDS, runs
+// A wavefront takes a chunk of 16 islands (at most 512 agents, 256 of the larger
+// genomes) into LDS, runs
 // generations t and t + 1 there and writes the chunk back. Within a generation
 // islands depend on each other only through the emissions of the one before,
 // so what the second generation needs from outside the chunk is its neighbours'
@@ -21,17 +22,18 @@
 // single-generation launch expects; the host runs them in fours.
 //
 // Bound: the matrix cores have nothing to do here; HBM (26 bytes per agent a
-// launch) and VALU (80 instructions per 64 children, 59 of them in the loop) are
-// both about 80 % busy. 1024 x 512 x 32, k = 2: 36 us per generation (72 a
-// launch, 6.0 TB/s) against 62 for the single-generation kernel; 300 x 200 x 64
-// trap-4 on the hybrid surface, k = 3: 23.9 against 34.2; it is ahead at every
+// launch, 6.1 of the 7.2 TB/s an in-place update reaches) and VALU (77
+// instructions per 64 children, 59 of them in the loop; 0.89 of the issue slots)
+// together. 1024 x 512 x 32, k = 2: 36 us per generation (72 a launch) against
+// 62 for the single-generation kernel; 300 x 200 x 64 trap-4 on the hybrid
+// surface, k = 3: 18.6 against 34.2; it is ahead at every
 // grid and island size from four members up (16 x 16 x 32: 1.8 against 3.2,
 // 4096 x 1024 x 32: 326 against 645). What made it so: arrivals and draws kept
 // in registers, four lanes an island, so that LDS holds 24 wavefronts a CU
 // instead of 18, and the neighbours' draws read, not drawn (43 -> 37 us);
 // workgroups of one wavefront (43.8 at four). Full chunks: 8 islands 42 us,
-// 4 islands 56. Unrolling the loop four times left it where it was; capping the
-// registers for a seventh wavefront per SIMD spills.
+// 4 islands 56. Unrolling the loop four times left it where it was; a register
+// cap for more wavefronts per SIMD where both loops share a kernel spills (43).
 #pragma once
 
 #include "ga_device.hpp"

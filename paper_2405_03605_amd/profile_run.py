@@ -1,15 +1,15 @@
 """Short runs with a fixed number of generations per kernel launch, so that a
 profiler's per-dispatch counters compare across dispatches (graphs off).
 
-  python -m paper_2405_03605_amd.profile_run paper-streaming   # 16.8M agents, one launch per generation
+  python -m paper_2405_03605_amd.profile_run paper-streaming   # 16.8M agents, two generations per launch
   python -m paper_2405_03605_amd.profile_run mid-tiles         # 256x256x32, LDS-resident tiles
-  python -m paper_2405_03605_amd.profile_run mid-streaming     # 256x256x32, one launch per generation
+  python -m paper_2405_03605_amd.profile_run mid-streaming     # 256x256x32, two generations per launch
   python -m paper_2405_03605_amd.profile_run batch             # the 64-run batched workload
   python -m paper_2405_03605_amd.profile_run batch-single      # one 1024x256x32 run, plain then batched
   python -m paper_2405_03605_amd.profile_run batch-classes     # per class: one run plain, then batched
 
 --gens is the generations per dispatch for mid-tiles (default 200) and the
-dispatch count otherwise (default 12); --launches the tile launches (default 4);
+generations in all otherwise (default 12, a multiple of four: two per dispatch); --launches the tile launches (default 4);
 --tiles WxH the tile shape of mid-tiles.
 """
 from __future__ import annotations
@@ -40,8 +40,10 @@ def _streaming(cfg, gens, torch, ipw=0, wpg=0):
     run.close()
 
 
-def _batch(runs, gens, torch):
+def _batch(runs, gens, torch, ipw=0):
     batch = GABatch()
+    if ipw:
+        batch.set_launch(ipw)
     for r in runs:
         batch.add(r, 10 ** 6)
     batch.set_graph_block(0)
@@ -85,20 +87,19 @@ def main():
         gens = args.gens or 12
         _batch([GARun(c) for c in batched_configs()], gens, torch)
     elif args.mode == "batch-classes":
-        # per class, in this order: `gens` plain dispatches, then `gens` batched,
-        # both with the batch's default shape (512 agents per wavefront, four
-        # wavefronts per group)
+        # per class, in this order: gens / 2 plain dispatches, then as many
+        # batched, both with full chunks (16 islands, at most 512 agents)
         gens = args.gens or 12
         for l, w in CLASS_RUNS:
             cfg = class_config(l, w)
             _streaming(cfg, gens, torch, ipw=512 >> l, wpg=4)
-            _batch([GARun(cfg)], gens, torch)
+            _batch([GARun(cfg)], gens, torch, ipw=512 >> l)
     else:
         gens = args.gens or 12
         cfg = run_config(width=1024, height=256, pop=32, sites=32, seed=1)
         _streaming(cfg, gens, torch)
         _batch([GARun(cfg)], gens, torch)
-    print(f"{args.mode}: {gens} generations per dispatch", flush=True)
+    print(f"{args.mode}: {gens} generations", flush=True)
 
 
 if __name__ == "__main__":

@@ -205,7 +205,7 @@ class GARun:
 
 
 class GABatch:
-    """Many runs advanced together: one launch per generation over every
+    """Many runs advanced together: two generations per launch over every
     member's islands, blocks of generations replayed from a HIP graph."""
 
     def __init__(self, stream=None):

@@ -2,7 +2,7 @@
 
 Requests (a run configuration and a generation budget) arrive over time. The
 server keeps every admitted run's state on the device and advances all of them
-together in the batched form (one launch per generation over every member's
+together in the batched form (two generations per launch over every member's
 islands, blocks of generations replayed from a HIP graph). Between blocks it
 retires runs whose budget is spent (their end-population surfaces are sampled,
 one agent per island, as in the paper's Sec. 3 end-state sampling), which frees
