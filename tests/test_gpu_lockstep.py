@@ -62,3 +62,23 @@ def test_streamed_lockstep_leaves_what_the_persistent_launch_does(edge):
         assert (la == lb).all()
     for name in ("f", "T", "D"):
         assert np.array_equal(pair[0][1][name].view(np.uint32), pair[1][1][name].view(np.uint32))
+
+
+def test_streamed_lockstep_past_2_32_generations():
+    edge = dict(width=24, height=17, pop=32, sites=32, k=2, seed=97)
+    say(f"lockstep past 2^32 generations, {edge}")
+    out = []
+    for cap in (0, 1024):
+        run = GARun(run_config(schedule=SCHEDULE_ASYNC, **edge))
+        run.step(3)
+        got = run.read()
+        run.write(got["f"], got["T"], got["D"], None, 2 ** 32 - 30)
+        run.set_async(cap)
+        run.step(60)
+        out.append((run.async_taken(), run.async_last_taken().copy(), run.read()))
+        assert run.async_waits() == 0
+        run.close()
+    assert out[0][0] == out[1][0]
+    assert (out[0][1] == out[1][1]).all()
+    for name in ("f", "T", "D"):
+        assert np.array_equal(out[0][2][name].view(np.uint32), out[1][2][name].view(np.uint32))

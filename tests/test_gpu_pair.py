@@ -4,6 +4,7 @@ last island or come short of a wavefront's planes; every policy, string model
 and tournament size; from generations of every remainder by four, in one step,
 in captured blocks and over an outbox and a population set from outside; and
 batches of them, whose members end at every remainder by four."""
+import numpy as np
 import pytest
 
 import oracle
@@ -152,3 +153,34 @@ def test_pool_runs_take_pairs():
         f, rT, rD = oracle_after(c, budget).population()
         assert (T == rT[ids]).all() and (D == rD.reshape(len(rT), -1)[ids]).all()
     pool.close()
+
+
+@pytest.mark.parametrize("edge", [dict(pop=32, sites=32, k=2), dict(pop=16, sites=64, k=4, policy=2)],
+                         ids=lambda e: "-".join(f"{k}{v}" for k, v in e.items()))
+def test_pairs_past_2_32_generations_from_any_population(edge):
+    """Ranks of every size, infinite fitness, and the generation counter's high word."""
+    cfg = run_config(width=37, height=23, seed=78, **edge)
+    say(f"pairs past 2^32 generations, {cfg}")
+    rng = np.random.default_rng(78)
+    n = 37 * 23 * edge["pop"]
+    f = rng.integers(-8, 8, n).astype(np.float32) / 2
+    f[rng.random(n) < 0.02] = np.inf
+    f[rng.random(n) < 0.02] = -np.inf
+    T = (rng.integers(0, 2 ** 32, n, dtype=np.uint64) >> rng.integers(0, 32, n, dtype=np.uint64))
+    T = np.minimum(T, 2 ** 31).astype(np.uint32)
+    D = rng.integers(0, 2 ** 32, (n, edge["sites"] // 32), dtype=np.uint64).astype(np.uint32)
+    start = 2 ** 32 - 9
+    run = GARun(cfg)
+    run.set_launch(form=FORM_STREAMING)
+    run.step(4)
+    ob = run.read()["outbox"]
+    run.write(f, T, D, ob, start)
+    run.set_graph_block(8)
+    run.step(21)
+    ref = oracle.OracleRun(cfg)
+    ref.set_population(f, T, D)
+    ref.set_outbox(ob["valid"], ob["dir"], ob["f"], ob["T"], ob["D"])
+    ref.set_generation(start)
+    ref.step(21)
+    assert_same_state(run.read(), ref, "past 2^32")
+    run.close()
