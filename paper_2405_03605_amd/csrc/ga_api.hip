@@ -503,9 +503,14 @@ int step_tiles(ga_run* r, uint64_t n) {
       alone ? 1
             : std::max<uint64_t>(1, std::min<uint64_t>(1u << 16,
                                                        (1ull << 34) / std::max(1u, v.agents)));
+  // Without migration no tile waits for another, so the outbox plane that a launch
+  // ends on must not be the one that its tiles start from: the planes alternate,
+  // so such launches run an odd number of generations.
+  const bool odd = n_tiles > 1 && !v.migration;
   uint64_t left = n;
   while (left > 0) {
-    const uint64_t slice = std::min(left, slice_max);
+    uint64_t slice = std::min(left, slice_max);
+    if (odd && slice % 2 == 0) slice -= 1;
     GA_HIP(ga::launch_tiles(v, slice, r->stream), "tile launch");
     GA_HIP(ga::launch_advance(v.gen, slice, r->stream), "advance launch");
     left -= slice;

@@ -41,7 +41,11 @@
 // which the iterations hide (the reader's first try goes out halfway through
 // them). A slot is overwritten two generations later, after its owner has
 // read the emission of t+1 of every neighbour outside its tile, which each of
-// them sends only after reading the slot.
+// them sends only after reading the slot. The same order keeps a tile that is
+// done from writing its last emissions over the pending ones of the HBM outbox
+// that a neighbour has yet to read (the same plane after an even number of
+// generations); without migration nothing is sent, and the host runs an odd
+// number of generations a launch.
 //
 // Every tile's workgroup must be resident at once (the host sizes the tiling
 // by the occupancy query); each wait on another tile is bounded, and a wait

@@ -1,0 +1,94 @@
+"""Which launches the C ABI's host logic plans, on the CPU: ga_api.hip built with
+g++ against stand-ins (tests/host_plan) that carry each launch out as the
+generations it would run, on launches and graphs alike, and abort where an agent
+is not at the generation a launch says or its candidates are not there."""
+import ctypes
+import os
+import subprocess
+
+import numpy as np
+import pytest
+
+from paper_2405_03605_amd import _lib
+from paper_2405_03605_amd.run import _fields, make_config
+from paper_2405_03605_amd.workloads import run_config
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+P = ctypes.c_void_p
+
+
+@pytest.fixture(scope="module")
+def lib(tmp_path_factory):
+    so = str(tmp_path_factory.mktemp("plan") / "libga_host_plan.so")
+    csrc = os.path.join(ROOT, "paper_2405_03605_amd", "csrc")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-fPIC", "-shared", "-Wl,-Bsymbolic",
+                    "-I" + os.path.join(ROOT, "tests", "host_mock"), "-I" + csrc,
+                    "-I" + os.path.join(ROOT, "include"), "-I/opt/rocm/include",
+                    "-x", "c++", os.path.join(csrc, "ga_api.hip"),
+                    "-x", "c++", os.path.join(ROOT, "tests", "host_plan", "plan_hip.cpp"),
+                    "-o", so], check=True, capture_output=True, timeout=600)
+    lib = ctypes.CDLL(so)
+    for name, (res, args) in _lib.SIGNATURES.items():
+        f = getattr(lib, name)
+        f.restype, f.argtypes = res, args
+    lib.plan_reset.argtypes = [ctypes.c_size_t]
+    lib.plan_reset.restype = None
+    lib.plan_count.argtypes = [ctypes.c_char_p]
+    lib.plan_tile_gens.restype = ctypes.c_uint64
+    lib.plan_reset((1 << 64) - 1)
+    return lib
+
+
+class Run:
+    """A run in host memory."""
+
+    def __init__(self, lib, **kw):
+        self.lib, self.cfg = lib, run_config(**kw)
+        c = make_config(_fields(self.cfg))
+        n = lib.ga_state_bytes(ctypes.byref(c))
+        assert n > 0
+        raw = np.zeros(n + 256, np.uint8)
+        self.mem = raw[(-raw.ctypes.data) % 256:][:n]
+        self.h = P()
+        assert lib.ga_init(ctypes.byref(c), P(self.mem.ctypes.data), n, None,
+                           ctypes.byref(self.h)) == 0
+        self.agents = self.cfg["width"] * self.cfg["height"] * self.cfg["pop"]
+
+    def step(self, n):
+        assert self.lib.ga_step(self.h, n) == 0
+
+    def ran(self):
+        """The generation every agent is at."""
+        T, g = np.empty(self.agents, np.uint32), ctypes.c_uint64()
+        assert self.lib.ga_read_population(self.h, None, P(T.ctypes.data), None, None,
+                                           ctypes.byref(g)) == 0
+        assert (T == T[0]).all() and T[0] == g.value & 0xFFFFFFFF
+        return g.value
+
+    def close(self):
+        self.lib.ga_destroy(self.h)
+
+
+def tile_launches(lib):
+    return [lib.plan_tile_gens(i) for i in range(lib.plan_count(b"tile launches"))]
+
+
+@pytest.mark.parametrize("n", [1, 2, 3, 4, 100, 70000])
+def test_closed_islands_in_several_tiles_end_on_the_other_outbox_plane(lib, n):
+    # without migration tiles do not wait for each other, so a launch must not
+    # write the outbox plane that its tiles read pending emissions from: the
+    # planes alternate, so it runs an odd number of generations
+    r = Run(lib, width=16, height=16, pop=32, migration=0)
+    assert lib.ga_set_launch(r.h, 0, 0, _lib.FORM_RESIDENT) == 0
+    assert lib.ga_set_tiles(r.h, 8, 8) == 0
+    lib.plan_reset((1 << 64) - 1)
+    r.step(n)
+    assert r.ran() == n
+    gens = tile_launches(lib)
+    assert sum(gens) == n and all(g % 2 == 1 for g in gens)
+    # one tile, and open islands, whose tiles wait, run in as few as before
+    assert lib.ga_set_tiles(r.h, 16, 16) == 0
+    lib.plan_reset((1 << 64) - 1)
+    r.step(n)
+    assert len(tile_launches(lib)) == -(-n // 65536)
+    r.close()
