@@ -342,6 +342,24 @@ void pool_give(ga_pool* p, size_t off, size_t size) {
   p->free_blocks.emplace(off, size);
 }
 
+// hipMalloc for memory that the library holds itself. Not part of what a stream
+// captures, so the calling thread's capture mode is relaxed for it: otherwise an
+// allocation fails, and ends any capture in progress with an error, be it this
+// stream's or another thread's. (The host-only build of the tests captures
+// nothing.)
+hipError_t device_malloc(void** p, size_t bytes) {
+#ifdef __HIP__
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  const hipError_t e = hipThreadExchangeStreamCaptureMode(&mode);
+  if (e != hipSuccess) return e;
+  const hipError_t rc = hipMalloc(p, bytes);
+  (void)hipThreadExchangeStreamCaptureMode(&mode);
+  return rc;
+#else
+  return hipMalloc(p, bytes);
+#endif
+}
+
 uint32_t per_iter(const ga_run* r) { return 64u >> r->view.log2n; }
 
 constexpr uint32_t kFullWaves = 4096;
@@ -738,7 +756,7 @@ void alloc_own(ga_run* r) {
                           : resident ? 2 * (size_t)v.islands * ga::exchange_words(strings) * 8
                                      : 0;
   void* p = nullptr;
-  if (hipMalloc(&p, cand + exchange) != hipSuccess) {
+  if (device_malloc(&p, cand + exchange) != hipSuccess) {
     (void)hipGetLastError();
     return;
   }
@@ -1465,7 +1483,7 @@ int rebuild_tables(ga_batch* b) {
     b->d_cand = nullptr;
     b->cand_cap = 0;
     void* p = nullptr;
-    if (hipMalloc(&p, 2 * need) == hipSuccess) {
+    if (device_malloc(&p, 2 * need) == hipSuccess) {
       b->d_cand = static_cast<uint8_t*>(p);
       b->cand_cap = 2 * need;
     } else {
