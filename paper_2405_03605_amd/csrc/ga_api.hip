@@ -9,6 +9,7 @@
 #include <cstdio>
 #include <cstring>
 #include <map>
+#include <mutex>
 #include <new>
 #include <string>
 #include <vector>
@@ -205,6 +206,13 @@ Layout layout_of(const ga_config* c) {
   return L;
 }
 
+// A block of device memory that the library allocated.
+struct Own {
+  void* p = nullptr;
+  size_t bytes = 0;
+  int device = 0;
+};
+
 }  // namespace
 
 struct ga_run {
@@ -213,7 +221,7 @@ struct ga_run {
   Layout lay{};
   hipStream_t stream = nullptr;
   uint8_t* base = nullptr;
-  void* own = nullptr;  // view.cand and view.exchange, or async_ob
+  Own own;  // view.cand and view.exchange, or async_ob
   // asynchronous runs: two candidate planes, then two outbox planes for the
   // streaming form (NULL: none)
   uint32_t* async_ob = nullptr;
@@ -263,12 +271,11 @@ struct ga_batch {
   // headroom), largest islands per wavefront (sizes the LDS), group size
   uint32_t grid_waves = 0, use_max_ipw = 0, use_wpg = 0;
   // whether its launches take two generations: every member's islands have four
-  // agents or more, and its candidates (its own, or in d_cand for a pool's run)
+  // agents or more, and its candidates (its own, or in cand for a pool's run)
   // have a place. They are taken anew in each block, so the table's rebuild may
   // place them elsewhere.
   bool pairs = false;
-  uint8_t* d_cand = nullptr;
-  size_t cand_cap = 0;
+  Own cand;
   bool dirty = true;           // membership or shapes changed since the last upload
   bool graph_stale = true;     // the captured graph no longer matches
   hipStream_t capture_stream = nullptr;
@@ -358,6 +365,69 @@ hipError_t device_malloc(void** p, size_t bytes) {
 #else
   return hipMalloc(p, bytes);
 #endif
+}
+
+// Memory of the library's own, of a destroyed run or an outgrown batch, is kept
+// for the next one that asks for about as much: hipFree waits for every stream of
+// the device (ga_destroy took 76 ms behind that much work on another stream, 0.05
+// without it). At most kKeptBytes in kKeptBlocks; more goes back to the device, with
+// that wait, and everything kept does when an allocation fails. A block is given
+// only once nothing enqueued uses it, so any thread or stream may have it next.
+constexpr size_t kKeptBytes = 64u << 20;
+constexpr uint32_t kKeptBlocks = 64;
+std::mutex kept_mutex;
+Own kept[kKeptBlocks];
+uint32_t n_kept = 0;
+size_t kept_bytes = 0;
+
+// Of the current device's kept blocks one that holds `bytes` (under twice as
+// large; any at all for bytes = 0). p is NULL if there is none.
+Own kept_take(int device, size_t bytes) {
+  std::lock_guard<std::mutex> hold(kept_mutex);
+  for (uint32_t k = 0; k < n_kept; ++k) {
+    if (kept[k].device != device) continue;
+    if (bytes && (kept[k].bytes < bytes || kept[k].bytes / 2 > bytes)) continue;
+    const Own b = kept[k];
+    kept[k] = kept[--n_kept];
+    kept_bytes -= b.bytes;
+    return b;
+  }
+  return Own();
+}
+
+// At least `bytes` on the current device; p is NULL without memory.
+Own own_take(size_t bytes) {
+  int device = 0;
+  if (hipGetDevice(&device) != hipSuccess) return Own();
+  Own b = kept_take(device, bytes);
+  while (!b.p) {
+    if (device_malloc(&b.p, bytes) == hipSuccess) {
+      b.bytes = bytes;
+      b.device = device;
+      return b;
+    }
+    (void)hipGetLastError();
+    b.p = nullptr;
+    const Own spare = kept_take(device, 0);
+    if (!spare.p) return Own();
+    (void)hipFree(spare.p);
+  }
+  return b;
+}
+
+void own_give(Own& b) {
+  if (!b.p) return;
+  bool keep = false;
+  {
+    std::lock_guard<std::mutex> hold(kept_mutex);
+    keep = n_kept < kKeptBlocks && kept_bytes + b.bytes <= kKeptBytes;
+    if (keep) {
+      kept[n_kept++] = b;
+      kept_bytes += b.bytes;
+    }
+  }
+  if (!keep) (void)hipFree(b.p);
+  b = Own();
 }
 
 uint32_t per_iter(const ga_run* r) { return 64u >> r->view.log2n; }
@@ -755,19 +825,15 @@ void alloc_own(ga_run* r) {
   const size_t exchange = async      ? cand
                           : resident ? 2 * (size_t)v.islands * ga::exchange_words(strings) * 8
                                      : 0;
-  void* p = nullptr;
-  if (device_malloc(&p, cand + exchange) != hipSuccess) {
-    (void)hipGetLastError();
-    return;
-  }
-  r->own = p;
+  r->own = own_take(cand + exchange);
+  if (!r->own.p) return;
   if (async) {
-    r->async_ob = static_cast<uint32_t*>(p);
+    r->async_ob = static_cast<uint32_t*>(r->own.p);
     return;
   }
-  v.cand = static_cast<uint32_t*>(p);
+  v.cand = static_cast<uint32_t*>(r->own.p);
   if (resident)
-    v.exchange = reinterpret_cast<unsigned long long*>(static_cast<uint8_t*>(p) + cand);
+    v.exchange = reinterpret_cast<unsigned long long*>(static_cast<uint8_t*>(r->own.p) + cand);
 }
 
 // Empty the exchange area of a run at generation t.
@@ -847,10 +913,8 @@ int init_run(const ga_config* cfg, void* dev_mem, size_t bytes, void* hip_stream
     e = clear_exchange(v, 0, r->stream);
   }
   if (e != hipSuccess) {
-    if (r->own) {
-      (void)hipStreamSynchronize(r->stream);
-      (void)hipFree(r->own);
-    }
+    if (r->own.p) (void)hipStreamSynchronize(r->stream);
+    own_give(r->own);
     delete r;
     return hip_fail(e, "init fill");
   }
@@ -1208,10 +1272,13 @@ int ga_extract_surfaces(ga_run* r, const uint64_t* agent_ids, size_t n, uint64_t
 void ga_destroy(ga_run* r) {
   if (!r) return;
   if (r->batch) ga_batch_remove(r->batch, r);
-  (void)hipStreamSynchronize(r->stream);
+  const bool idle = hipStreamSynchronize(r->stream) == hipSuccess;
   drop_graph(r);
   if (r->capture_stream) (void)hipStreamDestroy(r->capture_stream);
-  if (r->own) (void)hipFree(r->own);
+  if (idle)
+    own_give(r->own);
+  else
+    (void)hipFree(r->own.p);
   delete r;
 }
 
@@ -1477,19 +1544,11 @@ int rebuild_tables(ga_batch* b) {
     if (r->view.log2n < ga::kPairMinLog) pairs = false;
     if (r->view.migration && !r->view.cand) need += cand_bytes(r->view);
   }
-  if (pairs && need > b->cand_cap) {
+  if (pairs && need > b->cand.bytes) {
     GA_HIP(hipStreamSynchronize(b->stream), "stream sync");
-    if (b->d_cand) GA_HIP(hipFree(b->d_cand), "free candidates");
-    b->d_cand = nullptr;
-    b->cand_cap = 0;
-    void* p = nullptr;
-    if (device_malloc(&p, 2 * need) == hipSuccess) {
-      b->d_cand = static_cast<uint8_t*>(p);
-      b->cand_cap = 2 * need;
-    } else {
-      (void)hipGetLastError();
-      pairs = false;  // no memory left: one generation per launch
-    }
+    own_give(b->cand);
+    b->cand = own_take(2 * need);
+    if (!b->cand.p) pairs = false;  // no memory left: one generation per launch
   }
   if (pairs != b->pairs) b->graph_stale = true;
   b->pairs = pairs;
@@ -1517,7 +1576,7 @@ int rebuild_tables(ga_batch* b) {
     ga::RunView v = b->members[m]->view;
     v.ipw = chunk(v, halvings);
     if (pairs && v.migration && !v.cand) {
-      v.cand = reinterpret_cast<uint32_t*>(b->d_cand + placed);
+      v.cand = reinterpret_cast<uint32_t*>(static_cast<uint8_t*>(b->cand.p) + placed);
       placed += cand_bytes(v);
     }
     max_ipw = std::max(max_ipw, v.ipw);
@@ -1745,7 +1804,7 @@ void ga_batch_destroy(ga_batch* b) {
     if (b->stage_done[i]) (void)hipEventDestroy(b->stage_done[i]);
   }
   if (b->d_tab) (void)hipFree(b->d_tab);
-  if (b->d_cand) (void)hipFree(b->d_cand);
+  own_give(b->cand);
   delete b;
 }
 

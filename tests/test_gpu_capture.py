@@ -1,6 +1,7 @@
 """Runs created while a stream is being captured: on the capturing stream (the
 founders and the steps are then part of the graph, so every replay starts over) and
-on another thread and stream, whose allocations must not end the capture."""
+on another thread and stream, whose allocations must not end the capture. And
+destroyed while another stream is busy, which they must not wait for."""
 import ctypes
 import threading
 
@@ -82,3 +83,27 @@ def test_run_created_while_another_thread_captures():
     assert codes == [0] and float(x[0]) == 4.0
     assert lib.ga_step(h, 8) == 0
     lib.ga_destroy(h)
+
+
+def test_destroying_a_run_does_not_wait_for_other_streams():
+    say("destroy beside another stream's work")
+    cfg = run_config(width=40, height=24, pop=32, sites=32, k=2, seed=73)
+    a = torch.randn(8192, 8192, device="cuda", dtype=torch.bfloat16)
+    busy, done = torch.cuda.Stream(), torch.cuda.Event()
+    runs = [GARun(cfg) for _ in range(3)]
+    for r in runs:
+        r.step(6)
+    torch.cuda.synchronize()
+    with torch.cuda.stream(busy):
+        for _ in range(200):
+            b = a @ a
+        done.record(busy)
+    for r in runs:
+        r.close()
+    again = GARun(cfg)     # takes what they left
+    again.step(21)
+    got = again.read()
+    assert not done.query(), "the other stream's work was waited for"
+    assert_same_state(got, oracle_after(cfg, 21), "run in memory taken over")
+    again.close()
+    assert torch.isfinite(b[0, 0])

@@ -92,3 +92,37 @@ def test_closed_islands_in_several_tiles_end_on_the_other_outbox_plane(lib, n):
     r.step(n)
     assert len(tile_launches(lib)) == -(-n // 65536)
     r.close()
+
+
+def test_a_destroyed_run_leaves_its_memory_to_the_next(lib):
+    # freeing device memory waits for every stream of the device, so a small
+    # run's destruction frees nothing; what is kept is bounded and is given back
+    # when an allocation fails
+    kw = dict(width=40, height=24, pop=32)
+    Run(lib, **kw).close()
+    lib.plan_reset((1 << 64) - 1)
+    for _ in range(5):
+        a, b = Run(lib, **kw), Run(lib, **kw)
+        for r in (a, b):
+            r.step(9)
+            assert r.ran() == 9
+            r.close()
+    assert lib.plan_count(b"mallocs") <= 1 and lib.plan_count(b"frees") == 0
+    # no more than 64 MiB in at most 64 blocks: 70 runs at once, then gone
+    runs = [Run(lib, **kw) for _ in range(70)]
+    for r in runs:
+        r.close()
+    assert lib.plan_count(b"frees") >= 6
+    # larger than everything kept: allocated, and freed at once
+    lib.plan_reset((1 << 64) - 1)
+    big = Run(lib, width=1500, height=1024, pop=1)
+    big.close()
+    assert lib.plan_count(b"mallocs") == 1 and lib.plan_count(b"frees") == 1
+    # a failing allocation gives the kept blocks back before it gives up
+    lib.plan_reset(0)
+    r = Run(lib, width=60, height=60, pop=16)
+    assert lib.plan_count(b"frees") == 64
+    r.step(11)
+    assert r.ran() == 11
+    r.close()
+    lib.plan_reset((1 << 64) - 1)
