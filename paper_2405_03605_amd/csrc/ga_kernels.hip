@@ -607,7 +607,9 @@ void lockstep_kernel(RunView v, uint32_t chunks, uint64_t n_gens) {
 // is the buffer of parity t0 & 1, its entry (stamp included) is copied into
 // the one of parity (t0 - 1) & 1, which the lockstep exchange reads in
 // generation t0. The lockstep header of parity (t0 - 1) & 1 then reads 2 t0 if
-// there is a genome to take, 2 t0 + 1 if not.
+// there is a genome to take, 2 t0 + 1 if not. The header of the other parity may
+// be of any generation (the run set back to an earlier one since, or 2^30
+// generations behind): it becomes one that generation t0 + 1 waits on.
 __global__ void lockstep_prologue_kernel(RunView v, uint32_t t0) {
   const size_t k = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (k >= (size_t)v.islands * 4u) return;
@@ -623,6 +625,7 @@ __global__ void lockstep_prologue_kernel(RunView v, uint32_t t0) {
   if (e1 && (!e0 || (int32_t)(s1 - s0) > 0))
     for (uint32_t w = 0; w < v.ob_stride; ++w) read[w] = other[w];
   *lock_header(v.lock, j, d, p, v.island_stride) = (e0 || e1) ? due : due + 1u;
+  *lock_header(v.lock, j, d, p ^ 1u, v.island_stride) = due;
 }
 
 // The genomes of t - 1 of an asynchronous run whose islands all sent one (a
