@@ -65,6 +65,8 @@
 // in a pass between two workgroup barriers, per-tile progress words):
 // 256 x 256 x 32 5.9 to 4.45 (5.2 with the hardware's priority), 100 x 100 x 32
 // treatments 5.3 to 2.8, 37 x 23 x 16 k = 5 3.8 to 2.7, 8 x 8 x 32 2.6 to 1.7.
+#include <algorithm>
+
 #include "ga_device.hpp"
 
 namespace ga {
@@ -85,12 +87,12 @@ __host__ __device__ inline uint32_t tile_agents_padded(uint32_t ti_full, uint32_
 __host__ __device__ inline uint32_t tile_agent_words(uint32_t words, bool strings) {
   return 2u + words + (strings ? 2u : 0u);
 }
-// The product table, two words an island. The iterations read one block
-// ahead: past the last block that ends in the outbox and halo behind the
-// table (at least 96 bytes) for eight agents an island or more, in a block of
-// its own below. Padded so that what follows stays 16-byte aligned.
+// The product table, two words an island, padded so that what follows stays
+// 16-byte aligned. The iterations read one block ahead: past the last block that
+// ends in the outbox and halo behind the table (tile_lds_bytes has room for it
+// where those are shorter: a few islands of one or two agents).
 __host__ __device__ inline uint32_t tile_table_words(uint32_t ta, uint32_t log2n) {
-  return (2u * ((ta + (log2n < 3u ? 64u : 0u)) >> log2n) + 3u) & ~3u;
+  return (2u * (ta >> log2n) + 3u) & ~3u;
 }
 
 typedef uint32_t Quad __attribute__((ext_vector_type(4)));
@@ -557,9 +559,10 @@ size_t tile_lds_bytes(uint32_t tile_w, uint32_t tile_h, uint32_t log2n, uint32_t
                       uint32_t model, uint32_t ob_stride) {
   const uint32_t TI = tile_w * tile_h;
   const uint32_t TA = tile_agents_padded(TI, log2n);
-  return 4u * ((size_t)tile_agent_words(words, model_has_string(model)) * TA +
-               tile_table_words(TA, log2n) + 2u * (size_t)TI * ob_stride +
-               2u * (size_t)(tile_w + tile_h) * (ob_stride + 1u) + 2u);
+  const size_t pop = (size_t)tile_agent_words(words, model_has_string(model)) * TA;
+  const size_t all = pop + tile_table_words(TA, log2n) + 2u * (size_t)TI * ob_stride +
+                     2u * (size_t)(tile_w + tile_h) * (ob_stride + 1u) + 2u;
+  return 4u * std::max(all, pop + 2u * (size_t)((TA + 64u) >> log2n));
 }
 
 uint32_t tile_threads(uint32_t tile_w, uint32_t tile_h, uint32_t log2n) {

@@ -1,0 +1,51 @@
+"""The LDS-resident form at the edges of what it accepts, bit for bit against the
+oracle: tiles within 400 bytes of a CU's LDS, with islands of one, two and four
+agents, and tiles of a few such islands, whose read-ahead ends past their outbox."""
+import pytest
+
+from gpu_helpers import assert_same_state, oracle_after, say
+from paper_2405_03605_amd import FORM_RESIDENT, GARun
+from paper_2405_03605_amd.workloads import run_config
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    torch.cuda.set_device(0)
+    yield
+    torch.cuda.synchronize()
+
+
+def check(edge, tiles, steps=(1, 6)):
+    cfg = run_config(**edge)
+    say(f"tiles {tiles} on {cfg}")
+    run = GARun(cfg)
+    run.set_launch(form=FORM_RESIDENT)
+    run.set_tiles(*tiles)
+    assert run.tiles()[:2] == tiles
+    for n in steps:
+        run.step(n)
+    assert_same_state(run.read(), oracle_after(cfg, sum(steps)), f"tiles {tiles} {edge}")
+    run.close()
+
+
+@pytest.mark.parametrize("edge,tiles", [
+    (dict(width=2, height=1022, pop=1, sites=64, k=1), (1, 1022)),
+    (dict(width=4, height=612, pop=1, sites=64, k=1, model=1), (2, 612)),
+    (dict(width=4, height=581, pop=2, sites=64, k=2), (2, 581)),
+    (dict(width=7, height=375, pop=2, sites=64, k=3, model=2), (3, 375)),
+    (dict(width=10, height=217, pop=4, sites=64, k=2), (5, 217)),
+], ids=lambda e: f"N{e['pop']}m{e.get('model', 0)}" if isinstance(e, dict) else f"t{e[0]}x{e[1]}")
+def test_tiles_that_fill_the_lds(edge, tiles):
+    check(edge, tiles)
+
+
+@pytest.mark.parametrize("pop", [1, 2, 4])
+@pytest.mark.parametrize("sites,model", [(32, 0), (64, 0), (64, 1)])
+def test_tiles_of_a_few_islands(pop, sites, model):
+    check(dict(width=3, height=4, pop=pop, sites=sites, model=model, k=1, seed=81), (1, 1))
+    check(dict(width=7, height=5, pop=pop, sites=sites, model=model, k=1, seed=82), (3, 2))
