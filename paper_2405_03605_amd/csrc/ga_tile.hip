@@ -330,7 +330,15 @@ void tile_kernel(RunView v, uint32_t n_gens) {
         lds_put(to + 16u, Quad{hdr, 0u, 0u, 0u});
     }
   };
-  // fetch and settle, as often as it takes (one long wait at most)
+  // fetch and settle, as often as it takes (one long wait at most). Between tries
+  // a wavefront of the dense form sleeps (1.7 us) at the lowest priority, one of the
+  // plain form after 16 of them: 20 wavefronts of a CU that retry at once keep its
+  // one address unit busy, and a wavefront whose stores some of them wait for gets
+  // no turn until their tries run out (islands of one agent in 20 one-wavefront
+  // tiles a CU: single passes held up for 30 to 52 ms, the run invalid). 24 such
+  // tiles a CU: 13.5 us per generation, 18.8 asleep for half as long, 43 and more
+  // for a quarter or after 16 tries; 12 two-wavefront tiles of 32-agent islands 3.67
+  // against 3.55.
   uint32_t gave_up = 0u;
   auto wait_for = [&](bool on, uint32_t from, uint32_t stamp, uint32_t pair) {
     for (uint32_t spin = gave_up ? kLockSpins : 0u;; ++spin) {
@@ -340,6 +348,10 @@ void tile_kernel(RunView v, uint32_t n_gens) {
         gave_up += spin == kLockSpins ? 1u : 0u;
         settle(on, pair, s);
         break;
+      }
+      if (DENSE || spin >= 16u) {
+        __builtin_amdgcn_s_setprio(0);
+        __builtin_amdgcn_s_sleep(64);
       }
     }
   };

@@ -49,3 +49,15 @@ def test_tiles_that_fill_the_lds(edge, tiles):
 def test_tiles_of_a_few_islands(pop, sites, model):
     check(dict(width=3, height=4, pop=pop, sites=sites, model=model, k=1, seed=81), (1, 1))
     check(dict(width=7, height=5, pop=pop, sites=sites, model=model, k=1, seed=82), (3, 2))
+
+
+def test_many_waiting_wavefronts_a_cu():
+    # 24 one-wavefront tiles on every CU: most wait for a neighbour at any time,
+    # and the ones waited for must still get their turn
+    import torch
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    check(dict(width=8 * 24 * cus // 64, height=8 * 64, pop=1, sites=32, k=1, seed=84), (8, 8),
+          (60, 40))
+    # and of two wavefronts each, 32-agent islands
+    check(dict(width=2 * 10 * cus // 64, height=2 * 64, pop=32, sites=32, k=2, seed=85), (2, 2),
+          (60, 40))
