@@ -141,12 +141,15 @@ struct PassLane {
 };
 
 // DENSE: held to the registers of six wavefronts per SIMD (five with more than
-// one surface word or a string), for tilings of many small tiles that are only
-// all resident at that occupancy; it spills some. The plain form takes up to
-// 128 registers, four wavefronts per SIMD.
+// one surface word or a string, seven for islands of one agent), for tilings of
+// many small tiles that are only all resident at that occupancy; it spills some.
+// The plain form takes up to 128 registers, four wavefronts per SIMD.
+template <int LC, int SWC, typename Model>
+constexpr int kDenseWaves = SWC == 1 && !Model::kString ? (LC == 0 ? 7 : 6) : 5;
+
 template <bool DENSE, int LC, int SWC, typename Model, bool WIDE>
 __global__ __launch_bounds__(1024)
-__attribute__((amdgpu_waves_per_eu(DENSE ? (SWC == 1 && !Model::kString ? 6 : 5) : 4)))
+__attribute__((amdgpu_waves_per_eu(DENSE ? kDenseWaves<LC, SWC, Model> : 4)))
 void tile_kernel(RunView v, uint32_t n_gens) {
   constexpr uint32_t L = (uint32_t)LC;
   constexpr uint32_t SW = (uint32_t)SWC;

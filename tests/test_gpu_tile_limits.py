@@ -61,3 +61,12 @@ def test_many_waiting_wavefronts_a_cu():
     # and of two wavefronts each, 32-agent islands
     check(dict(width=2 * 10 * cus // 64, height=2 * 64, pop=32, sites=32, k=2, seed=85), (2, 2),
           (60, 40))
+
+
+@pytest.mark.parametrize("policy", [0, 1])
+def test_one_agent_islands_at_28_wavefronts_a_cu(policy):
+    import torch
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    # one-wavefront tiles, 28 on every CU
+    check(dict(width=8 * 28, height=8 * cus, pop=1, sites=32, k=1, policy=policy, seed=83), (8, 8),
+          (1, 40))
