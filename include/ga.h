@@ -414,8 +414,10 @@ int ga_batch_set_launch(ga_batch* batch, uint32_t islands_per_wave, uint32_t wav
  * rule, else a multiple of 64/N in [64/N, 64]. Results do not depend on it. */
 int ga_batch_set_class_launch(ga_batch* batch, uint32_t log2n, uint32_t words,
                               uint32_t islands_per_wave);
-/* The islands per wavefront a class uses and how many wavefront tiles its
- * current members make (either output may be NULL). */
+/* The islands per wavefront a class uses with the current members and settings
+ * and how many wavefront tiles its members make (either output may be NULL):
+ * under a setting the setting, cut to what a launch of two generations takes
+ * (above); set again, what this returns makes the same tiles. */
 int ga_batch_class_launch(ga_batch* batch, uint32_t log2n, uint32_t words,
                           uint32_t* islands_per_wave, uint32_t* tiles);
 void ga_batch_destroy(ga_batch* batch);

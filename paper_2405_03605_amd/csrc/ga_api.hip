@@ -275,6 +275,7 @@ struct ga_batch {
   // have a place. They are taken anew in each block, so the table's rebuild may
   // place them elsewhere.
   bool pairs = false;
+  uint32_t halvings = 0;       // of the default chunks (cut_ipw)
   Own cand;
   bool dirty = true;           // membership or shapes changed since the last upload
   bool graph_stale = true;     // the captured graph no longer matches
@@ -444,12 +445,11 @@ uint32_t default_ipw(const ga::RunView& v) {
   return std::max(g, std::min(64u, ipw));
 }
 
-// Of a chunk of v.ipw islands what a launch of two generations takes (in whole
-// iterations), and the bytes of a run's candidates.
-uint32_t pair_ipw(const ga::RunView& v) {
-  const uint32_t kw = ga::pair_words(v.words, ga::model_has_string_host(v.model));
-  const uint32_t ipw = std::min(v.ipw, ga::pair_agents(v.log2n, kw) >> v.log2n);
-  return ipw - ipw % (64u >> v.log2n);
+// Of a chunk of ipw islands of kw-word genomes what a launch of two generations
+// takes (in whole iterations), and the bytes of a run's candidates.
+uint32_t pair_ipw(uint32_t log2n, uint32_t kw, uint32_t ipw) {
+  const uint32_t most = std::min(ipw, ga::pair_agents(log2n, kw) >> log2n);
+  return most - most % (64u >> log2n);
 }
 size_t cand_bytes(const ga::RunView& v) { return 2 * (size_t)v.island_stride * v.ob_stride * 4; }
 
@@ -625,8 +625,7 @@ hipError_t launch_streaming(const ga_run* r, ga::RunView v, uint32_t n, hipStrea
   const uint32_t fours = pairs ? n & ~3u : 0u;
   hipError_t e = hipSuccess;
   if (fours) {
-    v.ipw = r->ipw;
-    v.ipw = pair_ipw(v);
+    v.ipw = pair_ipw(v.log2n, ga::pair_words(v.words, ga::model_has_string_host(v.model)), r->ipw);
     v.span = ga::kSpanCandidates;
     if (v.migration) e = ga::launch_generation(v, 0u, 1u, 1u, s);
     v.span = ga::kSpanTwo;
@@ -1437,9 +1436,9 @@ int ga_batch_settled(ga_batch* b, const ga_run* r, int* settled) {
 namespace {
 
 // Islands per wavefront of a class: its own setting, else the batch's, else
-// about 512 agents per wavefront whatever the island size (a batch has
-// wavefronts enough, so small members need no finer chunks, and short
-// wavefronts would spend their time in the per-wavefront set-up).
+// about 512 agents per wavefront whatever the island size (short wavefronts
+// spend their time in the per-wavefront set-up). cut_ipw has what launches of two
+// generations make of it.
 uint32_t class_ipw(const ga_batch* b, uint32_t c) {
   const uint32_t log2n = c / 2;
   const uint32_t g = 64u >> log2n;
@@ -1450,6 +1449,37 @@ uint32_t class_ipw(const ga_batch* b, uint32_t c) {
 }
 
 uint32_t class_of(const ga::RunView& v) { return v.log2n * 2u + v.words - 1u; }
+
+// How the members are cut into wavefronts' chunks: whether launches take two
+// generations, and then how often the chunks of classes without a setting are
+// halved, down to one iteration. As for a run alone that is as often as there are
+// under 4 wavefronts per SIMD (24 requests through 16 slots: 28.2 ms at full
+// chunks, 24.5, 23.9, 22.9 and 23.9 with at least 1024, 2048, 4096 and 8192
+// wavefronts).
+uint32_t cut_ipw(const ga_batch* b, bool pairs, uint32_t halvings, uint32_t c) {
+  const uint32_t log2n = c / 2u, words = c % 2u + 1u;
+  const uint32_t ipw = class_ipw(b, c);
+  if (!pairs || log2n < ga::kPairMinLog) return ipw;
+  const uint32_t most = pair_ipw(log2n, ga::pair_words(words, false), ipw);
+  if (b->ipw_override || b->cls[c].ipw) return most;
+  return std::max(64u >> log2n, most >> halvings);
+}
+uint32_t cut_halvings(const ga_batch* b, bool pairs) {
+  uint32_t halvings = 0;
+  for (; pairs && halvings < 4; ++halvings) {
+    uint64_t waves = 0;
+    for (const ga_run* r : b->members)
+      waves += ceil_div(r->view.islands, cut_ipw(b, pairs, halvings, class_of(r->view)));
+    if (waves >= kFullWaves) break;
+  }
+  return halvings;
+}
+// Whether every member's islands are large enough for two generations a launch.
+bool pairs_possible(const ga_batch* b) {
+  return !b->members.empty() &&
+         std::all_of(b->members.begin(), b->members.end(),
+                     [](const ga_run* r) { return r->view.log2n >= ga::kPairMinLog; });
+}
 
 extern "C++" {
 namespace {
@@ -1538,12 +1568,10 @@ int rebuild_tables(ga_batch* b) {
   std::vector<ga::Tile> tiles;
   views.reserve(b->members.size());
   uint32_t max_ipw = 1;
-  bool pairs = true;
+  bool pairs = pairs_possible(b);
   size_t need = 0, placed = 0;
-  for (const ga_run* r : b->members) {
-    if (r->view.log2n < ga::kPairMinLog) pairs = false;
+  for (const ga_run* r : b->members)
     if (r->view.migration && !r->view.cand) need += cand_bytes(r->view);
-  }
   if (pairs && need > b->cand.bytes) {
     GA_HIP(hipStreamSynchronize(b->stream), "stream sync");
     own_give(b->cand);
@@ -1552,29 +1580,11 @@ int rebuild_tables(ga_batch* b) {
   }
   if (pairs != b->pairs) b->graph_stale = true;
   b->pairs = pairs;
-  // chunks as for a run alone: where that leaves under 4 wavefronts per SIMD,
-  // classes without a setting of their own take shorter ones, down to one
-  // iteration (24 requests through 16 slots: 28.2 ms at full chunks, 24.5, 23.9,
-  // 22.9 and 23.9 with at least 1024, 2048, 4096 and 8192 wavefronts)
-  auto chunk = [&](const ga::RunView& view, uint32_t halvings) {
-    ga::RunView v = view;
-    v.ipw = class_ipw(b, class_of(v));
-    if (!pairs) return v.ipw;
-    v.ipw = pair_ipw(v);
-    if (b->ipw_override || b->cls[class_of(v)].ipw) return v.ipw;
-    return std::max(64u >> v.log2n, v.ipw >> halvings);
-  };
-  uint32_t halvings = 0;
-  for (; pairs && halvings < 4; ++halvings) {
-    uint64_t waves = 0;
-    for (const ga_run* r : b->members)
-      waves += ceil_div(r->view.islands, chunk(r->view, halvings));
-    if (waves >= kFullWaves) break;
-  }
+  b->halvings = cut_halvings(b, pairs);
   const uint32_t wpg = pairs ? 1u : b->wpg;
   for (uint32_t m = 0; m < b->members.size(); ++m) {
     ga::RunView v = b->members[m]->view;
-    v.ipw = chunk(v, halvings);
+    v.ipw = cut_ipw(b, pairs, b->halvings, class_of(v));
     if (pairs && v.migration && !v.cand) {
       v.cand = reinterpret_cast<uint32_t*>(static_cast<uint8_t*>(b->cand.p) + placed);
       placed += cand_bytes(v);
@@ -1735,10 +1745,14 @@ int ga_batch_class_launch(ga_batch* b, uint32_t log2n, uint32_t words, uint32_t*
   if (!b) return fail(GA_EINVAL, "batch is NULL");
   if (log2n > 6 || words < 1 || words > 2) return fail(GA_EINVAL, "no such class");
   const uint32_t c = log2n * 2 + words - 1;
+  // as the table has it, or as the next step will build it
+  const bool pairs = b->dirty ? pairs_possible(b) : b->pairs;
+  const uint32_t used =
+      cut_ipw(b, pairs, b->dirty ? cut_halvings(b, pairs) : b->halvings, c);
   uint32_t n = 0;
   for (const ga_run* r : b->members)
-    if (class_of(r->view) == c) n += ceil_div(r->view.islands, class_ipw(b, c));
-  if (ipw) *ipw = class_ipw(b, c);
+    if (class_of(r->view) == c) n += ceil_div(r->view.islands, used);
+  if (ipw) *ipw = used;
   if (tiles) *tiles = n;
   return GA_OK;
 }

@@ -26,6 +26,7 @@ size_t malloc_limit = SIZE_MAX;     // larger ones fail
 std::vector<size_t> mallocs;        // sizes asked for
 std::vector<uint64_t> tile_gens;    // generations of each tile launch
 unsigned frees = 0, captures = 0, persistent = 0;
+unsigned batch_tiles = 0;            // tiles of the last batch launch
 hipStream_t capturing = nullptr;
 ihipGraph_t* graph = nullptr;
 
@@ -55,6 +56,7 @@ unsigned plan_count(const char* what) {
   if (w == "frees") return frees;
   if (w == "captures") return captures;
   if (w == "persistent") return persistent;
+  if (w == "batch tiles") return batch_tiles;
   if (w == "tile launches") return (unsigned)tile_gens.size();
   stop("no such count");
 }
@@ -198,6 +200,7 @@ hipError_t launch_gather(const RunView& v, const uint32_t* ids, uint32_t n, uint
 hipError_t launch_batch_all(const RunView* views, const Tile* tiles, uint32_t grid, uint32_t off, uint32_t, uint32_t, hipStream_t s) {
   return run(s, [=] {
     std::map<uint32_t, bool> seen;
+    batch_tiles = (unsigned)std::count_if(tiles, tiles + grid, [](const Tile& t) { return t.cls != kNoTile; });
     for (uint32_t w = 0; w < grid; ++w) {
       const Tile tile = tiles[w];
       if (tile.cls == kNoTile) continue;

@@ -69,6 +69,26 @@ class Run:
         self.lib.ga_destroy(self.h)
 
 
+class Batch:
+    def __init__(self, lib, runs, budgets):
+        self.lib, self.h = lib, P()
+        assert lib.ga_batch_create(None, ctypes.byref(self.h)) == 0
+        for r, n in zip(runs, budgets):
+            assert lib.ga_batch_add(self.h, r.h, n) == 0
+
+    def step(self, n):
+        assert self.lib.ga_batch_step(self.h, n) == 0
+
+    def launch(self, log2n, words):
+        i, t = ctypes.c_uint32(), ctypes.c_uint32()
+        assert self.lib.ga_batch_class_launch(self.h, log2n, words, ctypes.byref(i),
+                                              ctypes.byref(t)) == 0
+        return i.value, t.value
+
+    def close(self):
+        self.lib.ga_batch_destroy(self.h)
+
+
 def tile_launches(lib):
     return [lib.plan_tile_gens(i) for i in range(lib.plan_count(b"tile launches"))]
 
@@ -126,3 +146,44 @@ def test_a_destroyed_run_leaves_its_memory_to_the_next(lib):
     assert r.ran() == 11
     r.close()
     lib.plan_reset((1 << 64) - 1)
+
+
+@pytest.mark.parametrize("shapes,chunks", [
+    # few islands: halved to one iteration; enough wavefronts: full chunks
+    ([dict(width=64, height=64, pop=8)], {(3, 2): 8}),
+    ([dict(width=256, height=256, pop=8, sites=32)], {(3, 1): 16}),
+    ([dict(width=64, height=64, pop=32, sites=32), dict(width=9, height=7, pop=64, migration=0),
+      dict(width=40, height=40, pop=4)], {(5, 1): 2, (6, 2): 1, (2, 2): 16}),
+    # an island of one agent: single generations, 512 agents a chunk
+    ([dict(width=9, height=7, pop=1), dict(width=64, height=64, pop=8)], {(0, 2): 64, (3, 2): 64}),
+])
+def test_class_launch_says_what_a_class_uses(lib, shapes, chunks):
+    def tiles_used(batch):
+        batch.step(5)
+        return lib.plan_count(b"batch tiles")
+
+    runs = [Run(lib, **s) for s in shapes]
+    batch = Batch(lib, runs, [1000] * len(runs))
+    before = {k: batch.launch(*k) for k in chunks}        # as the next step builds it
+    assert {k: i for k, (i, _) in before.items()} == chunks
+    assert tiles_used(batch) == sum(t for _, t in before.values())
+    assert {k: batch.launch(*k) for k in chunks} == before
+    # what was returned, set, makes the same tiles
+    for (l, w), i in chunks.items():
+        assert lib.ga_batch_set_class_launch(batch.h, l, w, i) == 0
+    assert {k: batch.launch(*k) for k in chunks} == before
+    assert tiles_used(batch) == sum(t for _, t in before.values())
+    # a setting beyond what a launch of two takes is cut to that
+    for (l, w), i in chunks.items():
+        assert lib.ga_batch_set_class_launch(batch.h, l, w, 64) == 0
+        used, n = batch.launch(l, w)
+        most = 64 if (0, 2) in chunks else {(3, 2): 16, (3, 1): 16, (5, 1): 16, (6, 2): 4,
+                                            (2, 2): 16}[(l, w)]
+        assert used == most
+    assert tiles_used(batch) == sum(batch.launch(*k)[1] for k in chunks)
+    for r in runs:
+        assert lib.ga_generation(r.h) == 15
+    batch.close()
+    for r in runs:
+        assert r.ran() == 15
+        r.close()
