@@ -221,7 +221,8 @@ def bench_batched(gens: int, torch, tune: bool = True):
     for r in runs:
         batch.add(r, gens + 100)
     chosen = autotune_batch(batch, cfgs) if tune else dict(
-        {k: batch.class_launch(*k)[0] for k in batch.classes()}, waves_per_group=4)
+        {k: batch.class_launch(*k)[0] for k in batch.classes()}, waves_per_group=4,
+        by_rule=tuple(batch.classes()))
     progress(f"batched leg: shapes {chosen}; timing {gens} generations")
     batch.step(100)
     torch.cuda.synchronize()
@@ -256,8 +257,10 @@ def bench_batched(gens: int, torch, tune: bool = True):
 def shape_names(chosen: dict) -> dict:
     """autotune_batch's choice with readable class names."""
     out = {"waves_per_group": chosen["waves_per_group"]}
-    out.update({f"N={1 << k[0]},words={k[1]}": {"islands_per_wave": v}
-                for k, v in sorted((k, v) for k, v in chosen.items() if k != "waves_per_group")})
+    by_rule = chosen.get("by_rule", ())
+    out.update({f"N={1 << k[0]},words={k[1]}":
+                {"islands_per_wave": v, "chosen": "rule" if k in by_rule else "timed"}
+                for k, v in sorted((k, v) for k, v in chosen.items() if isinstance(k, tuple))})
     return out
 
 

@@ -6,9 +6,10 @@ Single runs: islands per wavefront and wavefronts per workgroup of the
 streaming form, the LDS-resident form (its tile shapes), chosen by timing a
 scratch run of the same shape.
 
-Batches: per class of members (log2 N, surface words), the class kernel's
-islands per wavefront and wavefronts per workgroup, chosen by timing a scratch
-batch of that class's member shapes; cached by the class and its shapes.
+Batches: per class of members (log2 N, surface words) the islands per wavefront
+(and, where a batch takes one generation a launch, the batch's wavefronts per
+workgroup), chosen by timing a scratch batch of the members' shapes against the
+library's own rule; cached by the shapes.
 """
 from __future__ import annotations
 
@@ -162,11 +163,14 @@ BATCH_MARGIN = 0.01
 
 def autotune_batch(batch: GABatch, cfgs: list, gens: int = 300, use_cache: bool = True) -> dict:
     """Choose and apply the launch shape of a batch of runs with configurations
-    cfgs: the batch-wide wavefronts per workgroup, then each class's islands
-    per wavefront with the others held (coordinate descent), every candidate
-    timed (best of two) on a scratch batch of the same shapes in the launches
-    the batch runs, and taken only if it beats the shape in place by
-    BATCH_MARGIN. Returns {"waves_per_group": w, (log2 N, words): ipw}."""
+    cfgs: the batch-wide wavefronts per workgroup (where a member of one or two
+    agents an island keeps the batch to single generations; pairs go in groups of
+    one), then each class's islands per wavefront with the others held (coordinate
+    descent), every candidate that makes other chunks timed (best of two) on a
+    scratch batch of the same shapes in the launches the batch runs, and taken
+    only if it beats the shape in place, at first the library's rule, by
+    BATCH_MARGIN. Returns {"waves_per_group": w, (log2 N, words): ipw, "by_rule":
+    the classes left to the rule (their ipw is what it gives these members)}."""
     import torch
     key = _batch_key(cfgs)
     if not (use_cache and key in _batch_cache):
@@ -175,11 +179,11 @@ def autotune_batch(batch: GABatch, cfgs: list, gens: int = 300, use_cache: bool 
         scratch = GABatch()
         for r in runs:
             scratch.add(r, 1 << 40)
-        chosen = {k: scratch.class_launch(*k)[0] for k in classes}
         best_w = 4
         scratch.set_launch(0, best_w)
         best_t = _time_batch(scratch, gens, torch)
-        for w in WPG_CANDIDATES:
+        single = any(c["pop"] < 4 for c in cfgs)
+        for w in WPG_CANDIDATES if single else ():
             if w == best_w:
                 continue
             scratch.set_launch(0, w)
@@ -187,18 +191,25 @@ def autotune_batch(batch: GABatch, cfgs: list, gens: int = 300, use_cache: bool 
             if t < best_t * (1 - BATCH_MARGIN):
                 best_w, best_t = w, t
         scratch.set_launch(0, best_w)
+        by_rule = []
         for k in classes:
-            best_i = chosen[k]
+            best_i = 0
+            tried = {scratch.class_launch(*k)[0]}
             for ipw in batch_candidates(k[0]):
-                if ipw == best_i:
-                    continue
                 scratch.set_class_launch(k[0], k[1], ipw)
+                used = scratch.class_launch(*k)[0]
+                if used in tried:
+                    continue
+                tried.add(used)
                 t = _time_batch(scratch, gens, torch)
                 if t < best_t * (1 - BATCH_MARGIN):
                     best_i, best_t = ipw, t
             scratch.set_class_launch(k[0], k[1], best_i)
-            chosen[k] = best_i
+            if not best_i:
+                by_rule.append(k)
+        chosen = {k: scratch.class_launch(*k)[0] for k in classes}
         chosen["waves_per_group"] = best_w
+        chosen["by_rule"] = tuple(by_rule)
         scratch.close()
         for r in runs:
             r.close()
@@ -211,8 +222,9 @@ def autotune_batch(batch: GABatch, cfgs: list, gens: int = 300, use_cache: bool 
 def apply_shapes(target, chosen: dict):
     """Apply autotune_batch's choice to a GABatch or a GAPool (whose runs fall
     in the same classes): the group size, then each class's islands per
-    wavefront."""
+    wavefront, or the library's rule, which follows the live members."""
+    by_rule = chosen.get("by_rule", ())
     target.set_launch(0, chosen["waves_per_group"])
     for k, ipw in chosen.items():
-        if k != "waves_per_group":
-            target.set_class_launch(k[0], k[1], ipw)
+        if isinstance(k, tuple):
+            target.set_class_launch(k[0], k[1], 0 if k in by_rule else ipw)
