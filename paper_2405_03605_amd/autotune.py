@@ -56,13 +56,17 @@ def candidates(cfg: dict) -> list[tuple]:
 
 
 def tile_lds_estimate(tw: int, th: int, cfg: dict) -> int:
-    """LDS bytes of a tile of tw x th islands (16-byte agent records, 8 more
-    with a string; the island tables, both outbox parities, the halo)."""
+    """LDS bytes of a tile of tw x th islands: a plane of one word per agent for
+    each genome word (padded to 64 agents), a product of two words per island,
+    both outbox parities, the halo."""
     words = cfg["sites"] * cfg.get("dbits", 1) // 32
     strings = cfg.get("model", 0) != 0
     ob = 4 if words == 1 and not strings else 8
-    agents = -(-tw * th * cfg["pop"] // 64) * 64 + 2   # and two scratch records
-    return agents * (24 if strings else 16) + 8 * tw * th + 8 * tw * th * ob + 8 * (tw + th) * (ob + 1) + 16
+    agents = -(-tw * th * cfg["pop"] // 64) * 64
+    planes = (2 + words + 2 * strings) * agents
+    table = -(-2 * (agents // cfg["pop"]) // 4) * 4
+    return 4 * max(planes + table + 2 * tw * th * ob + 2 * (tw + th) * (ob + 1) + 2,
+                   planes + 2 * ((agents + 64) // cfg["pop"]))
 
 
 def apply(run: GARun, choice):

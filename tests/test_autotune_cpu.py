@@ -88,3 +88,18 @@ def test_group_size_is_searched_where_single_generations_run(tuner):
     FakeBatch.rule[(1, 2)] = FakeBatch.most[(1, 2)] = 64
     batch, chosen = tuner(lambda used, wpg: 1.0 / wpg, cfgs)
     assert chosen["waves_per_group"] == max(autotune.WPG_CANDIDATES)
+
+
+def test_tile_lds_estimate_is_the_kernels():
+    import ctypes
+
+    from paper_2405_03605_amd import _lib
+    lds = ctypes.CDLL(_lib.LIB_PATH)._ZN2ga14tile_lds_bytesEjjjjjj   # ga::tile_lds_bytes
+    lds.restype = ctypes.c_size_t
+    for pop in (1, 2, 4, 8, 16, 32, 64):
+        for sites, model in ((32, 0), (64, 0), (32, 1), (64, 2)):
+            cfg = run_config(pop=pop, sites=sites, model=model)
+            for tw, th in ((1, 1), (3, 2), (8, 8), (37, 5), (64, 24), (100, 13)):
+                want = lds(tw, th, pop.bit_length() - 1, sites // 32, model,
+                           4 if (sites, model) == (32, 0) else 8)
+                assert autotune.tile_lds_estimate(tw, th, cfg) == want, (pop, sites, model, tw, th)
