@@ -32,10 +32,16 @@ def candidates(cfg: dict) -> list[tuple]:
     FORM_STREAMING) and (tile_w, tile_h, FORM_RESIDENT) (0, 0: the library's
     tiling)."""
     per_iter = 64 // cfg["pop"]
+    words = cfg["sites"] * cfg.get("dbits", 1) // 32
+    two = cfg["pop"] >= 4      # two generations a launch: one wavefront a group
+    largest = 64
+    if two:                    # of a longer chunk those launches take as much
+        small = words > 1 or cfg.get("model", 0) != 0
+        largest = min(16, (256 if small else 512) // cfg["pop"])
     out = []
     ipw = per_iter
-    while ipw <= 64:
-        for wpg in (1, 2, 4, 8):
+    while ipw <= largest:
+        for wpg in ((4,) if two else (1, 2, 4, 8)):
             out.append((ipw, wpg, FORM_STREAMING))
         ipw *= 2
     out.append((0, 0, FORM_RESIDENT))

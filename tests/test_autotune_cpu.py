@@ -103,3 +103,22 @@ def test_tile_lds_estimate_is_the_kernels():
                 want = lds(tw, th, pop.bit_length() - 1, sites // 32, model,
                            4 if (sites, model) == (32, 0) else 8)
                 assert autotune.tile_lds_estimate(tw, th, cfg) == want, (pop, sites, model, tw, th)
+
+
+@pytest.mark.parametrize("kw,chunks", [
+    (dict(pop=32, sites=32), [2, 4, 8, 16]), (dict(pop=32, sites=64), [2, 4, 8]),
+    (dict(pop=64, sites=32), [1, 2, 4, 8]), (dict(pop=64, sites=32, model=1), [1, 2, 4]),
+    (dict(pop=16, sites=64), [4, 8, 16]), (dict(pop=4, sites=32), [16])])
+def test_single_run_candidates_are_the_chunks_that_differ(kw, chunks):
+    from paper_2405_03605_amd import FORM_STREAMING
+    cands = autotune.candidates(run_config(width=40, height=30, **kw))
+    streaming = [c for c in cands if c[2] == FORM_STREAMING]
+    assert streaming == [(i, 4, FORM_STREAMING) for i in chunks]
+    assert len(set(cands)) == len(cands)
+
+
+def test_single_generations_are_searched_in_both_directions():
+    from paper_2405_03605_amd import FORM_STREAMING
+    cands = autotune.candidates(run_config(width=40, height=30, pop=2))
+    assert {c[:2] for c in cands if c[2] == FORM_STREAMING} == {
+        (i, w) for i in (32, 64) for w in (1, 2, 4, 8)}
