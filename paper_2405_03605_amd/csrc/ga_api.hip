@@ -277,6 +277,7 @@ struct ga_batch {
   bool pairs = false;
   uint32_t halvings = 0;       // of the default chunks (cut_ipw)
   Own cand;
+  size_t cand_refused = SIZE_MAX;  // what could not be had; not asked for again
   bool dirty = true;           // membership or shapes changed since the last upload
   bool graph_stale = true;     // the captured graph no longer matches
   hipStream_t capture_stream = nullptr;
@@ -1474,9 +1475,18 @@ uint32_t cut_halvings(const ga_batch* b, bool pairs) {
   }
   return halvings;
 }
-// Whether every member's islands are large enough for two generations a launch.
+// Bytes of candidates that the batch has to place itself.
+size_t cand_need(const ga_batch* b) {
+  size_t need = 0;
+  for (const ga_run* r : b->members)
+    if (r->view.migration && !r->view.cand) need += cand_bytes(r->view);
+  return need;
+}
+// Whether launches take two generations: every member's islands are large enough
+// and, as far as is known, there is memory for the candidates.
 bool pairs_possible(const ga_batch* b) {
-  return !b->members.empty() &&
+  const size_t need = cand_need(b);
+  return !b->members.empty() && (need <= b->cand.bytes || need < b->cand_refused) &&
          std::all_of(b->members.begin(), b->members.end(),
                      [](const ga_run* r) { return r->view.log2n >= ga::kPairMinLog; });
 }
@@ -1569,13 +1579,14 @@ int rebuild_tables(ga_batch* b) {
   views.reserve(b->members.size());
   uint32_t max_ipw = 1;
   bool pairs = pairs_possible(b);
-  size_t need = 0, placed = 0;
-  for (const ga_run* r : b->members)
-    if (r->view.migration && !r->view.cand) need += cand_bytes(r->view);
+  const size_t need = cand_need(b);
+  size_t placed = 0;
   if (pairs && need > b->cand.bytes) {
     GA_HIP(hipStreamSynchronize(b->stream), "stream sync");
     own_give(b->cand);
-    b->cand = own_take(2 * need);
+    b->cand = own_take(2 * need);  // room for more members, if it can be had
+    if (!b->cand.p) b->cand = own_take(need);
+    b->cand_refused = b->cand.p ? SIZE_MAX : need;
     if (!b->cand.p) pairs = false;  // no memory left: one generation per launch
   }
   if (pairs != b->pairs) b->graph_stale = true;

@@ -187,3 +187,105 @@ def test_class_launch_says_what_a_class_uses(lib, shapes, chunks):
     for r in runs:
         assert r.ran() == 15
         r.close()
+
+
+class Pool:
+    def __init__(self, lib, nbytes, slots=64):
+        self.lib, self.h = lib, P()
+        raw = np.zeros(nbytes + 256, np.uint8)
+        self.mem = raw[(-raw.ctypes.data) % 256:][:nbytes]
+        assert lib.ga_pool_create(P(self.mem.ctypes.data), nbytes, slots, None,
+                                  ctypes.byref(self.h)) == 0
+
+    def admit(self, gens, **kw):
+        c, t = make_config(_fields(run_config(**kw))), ctypes.c_uint64()
+        assert self.lib.ga_pool_admit(self.h, ctypes.byref(c), gens, ctypes.byref(t)) == 0
+        return t.value, kw["width"] * kw["height"], gens
+
+    def step(self, n):
+        assert self.lib.ga_pool_step(self.h, n) == 0
+
+    def retire(self, run):
+        """Check that the run has run its generations, and let it go."""
+        ticket, islands, gens = run
+        ids, T = np.empty(islands, np.uint64), np.empty(islands, np.uint32)
+        D = np.empty((islands, 2), np.uint32)
+        assert self.lib.ga_pool_retire(self.h, ticket, P(ids.ctypes.data), P(T.ctypes.data),
+                                       P(D.ctypes.data)) == 0
+        assert (T == gens).all()
+
+
+SHAPES = [dict(width=30, height=20, pop=8), dict(width=17, height=9, pop=32, sites=32),
+          dict(width=64, height=5, pop=64, migration=0), dict(width=11, height=40, pop=16)]
+
+
+@pytest.mark.parametrize("block", [0, 4, 100])
+def test_a_pool_runs_every_budget_to_its_end(lib, block):
+    lib.plan_reset((1 << 64) - 1)
+    pool = Pool(lib, 1 << 24)
+    assert lib.ga_pool_set_graph_block(pool.h, block) == 0
+    live = []
+    for k, gens in enumerate((3, 100, 7, 250, 1, 42, 133, 64)):
+        live.append(pool.admit(gens, **SHAPES[k % 4]))
+        pool.step(50)
+    pool.step(400)
+    for run in live:
+        pool.retire(run)
+    lib.ga_pool_destroy(pool.h)
+
+
+def test_a_pool_without_memory_for_candidates(lib):
+    lib.plan_reset((1 << 64) - 1)
+    pool = Pool(lib, 1 << 24)
+    first = pool.admit(400, **SHAPES[0])
+    pool.step(20)                              # tables, and candidates of one run
+    need = 2 * (640 + 128) * 32                # of that run
+    # with every allocation failing, more members run one generation a launch, and
+    # what was refused is not asked for at every change of membership
+    lib.plan_reset(0)
+    live = [first]
+    asked = []
+    for k in range(6):
+        live.append(pool.admit(100, **SHAPES[k % 2]))
+        pool.step(4)
+        asked.append(lib.plan_count(b"mallocs"))
+    assert asked[-1] > 0 and len(set(asked)) <= 2
+    # fewer members again: that much is asked for, and had
+    lib.plan_reset((1 << 64) - 1)
+    pool.step(100)
+    for run in live[1:]:
+        pool.retire(run)
+    pool.step(7)
+    assert 1 <= lib.plan_count(b"mallocs") <= 2
+    # room for the members but not for as many again
+    lib.plan_reset(need * 5)
+    live = [first] + [pool.admit(60, **SHAPES[0]) for _ in range(3)]
+    pool.step(8)
+    assert lib.plan_count(b"mallocs") >= 2
+    assert lib.plan_count(b"batch tiles") == 4 * -(-600 // 8)   # chunks of a launch of two
+    pool.step(500)
+    for run in live:
+        pool.retire(run)
+    lib.ga_pool_destroy(pool.h)
+    lib.plan_reset((1 << 64) - 1)
+
+
+@pytest.mark.parametrize("limit", [0, (1 << 64) - 1])
+def test_single_runs_with_and_without_the_librarys_memory(lib, limit):
+    kw = dict(width=50, height=36, pop=32, sites=32)
+    Run(lib, width=49, height=35, pop=8).close()      # (frees what is kept, if it fails)
+    lib.plan_reset(limit)
+    streaming, tiles, lockstep = Run(lib, **kw), Run(lib, **kw), Run(lib, schedule=1, **kw)
+    assert lib.ga_set_launch(streaming.h, 0, 0, _lib.FORM_STREAMING) == 0
+    assert lib.ga_set_launch(tiles.h, 0, 0, _lib.FORM_RESIDENT) == 0
+    for r in (streaming, tiles, lockstep):
+        for n in (1, 4, 50, 231):
+            r.step(n)
+        assert r.ran() == 286
+    # tiles that exchange nothing run one generation a launch; the asynchronous run
+    # has the two ends of a call of 48 and more, or all of it, on the mail
+    assert lib.plan_count(b"tile launches") == (286 if limit == 0 else 4)
+    assert lib.plan_count(b"persistent") == (4 if limit == 0 else 6)
+    for r in (streaming, tiles, lockstep):
+        r.close()
+    lib.plan_reset((1 << 64) - 1)
