@@ -273,7 +273,8 @@ def test_a_pool_without_memory_for_candidates(lib):
 @pytest.mark.parametrize("limit", [0, (1 << 64) - 1])
 def test_single_runs_with_and_without_the_librarys_memory(lib, limit):
     kw = dict(width=50, height=36, pop=32, sites=32)
-    Run(lib, width=49, height=35, pop=8).close()      # (frees what is kept, if it fails)
+    lib.plan_reset(limit)
+    Run(lib, width=1500, height=1024, pop=1).close()  # where it fails, nothing stays kept
     lib.plan_reset(limit)
     streaming, tiles, lockstep = Run(lib, **kw), Run(lib, **kw), Run(lib, schedule=1, **kw)
     assert lib.ga_set_launch(streaming.h, 0, 0, _lib.FORM_STREAMING) == 0
