@@ -243,7 +243,7 @@ int ga_extract_surfaces(ga_run* run, const uint64_t* agent_ids, size_t n,
 uint64_t ga_generation(const ga_run* run);
 
 /* Release the handle (waits for the run's stream; only a run whose own memory
- * is beyond what the library keeps for later runs, 64 MiB, makes it wait for the
+ * is beyond what the library keeps for later runs, 256 MiB, makes it wait for the
  * device). The caller's device memory stays with the caller. A graph captured
  * from the run's steps must not be replayed after it. NULL is allowed. */
 void ga_destroy(ga_run* run);

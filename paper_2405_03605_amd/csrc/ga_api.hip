@@ -375,8 +375,8 @@ hipError_t device_malloc(void** p, size_t bytes) {
 // without it). At most kKeptBytes in kKeptBlocks; more goes back to the device, with
 // that wait, and everything kept does when an allocation fails. A block is given
 // only once nothing enqueued uses it, so any thread or stream may have it next.
-constexpr size_t kKeptBytes = 64u << 20;
-constexpr uint32_t kKeptBlocks = 64;
+constexpr size_t kKeptBytes = 256u << 20;
+constexpr uint32_t kKeptBlocks = 1024;
 std::mutex kept_mutex;
 Own kept[kKeptBlocks];
 uint32_t n_kept = 0;
