@@ -470,7 +470,14 @@ constexpr size_t kMaxGroupLds = 160 * 1024;
 // 37 x 23 x 16: 1.65 1.66 1.64 1.73 2.07 2.32 2.88), until CUs have two tiles
 // (64 x 64 x 32 in 256 tiles: 1.78, in 512: 1.84, in 2048: 2.95; 100 x 100 x 32
 // in 169: 2.35, in 1250: 2.58). Without such a tiling kMinDenseTileAgents holds.
+// Islands of one or two agents count as kSmallIsland of them: a wavefront's pass
+// covers 16 islands, so 64 agents of those take four passes or two in turn (40 x
+// 40 x 1 in tiles of 1,600, 800, 400, 128, 64, 32 and 16 islands: 6.20 3.02 2.67 2.43
+// 2.36 1.74 1.45 us; 30 x 30 x 2 in tiles of 900, 225, 128, 64, 32 and 16: 3.51 2.00
+// 1.83 1.78 1.73 1.42), and one tile of them waits longer for itself than 16-island
+// tiles for each other (10 x 10 x 1: 2.44 against 1.43, 20 x 10 x 2: 1.81, 1.46).
 constexpr uint32_t kOneTileAgents = 2048, kMinTileAgents = 128, kMinDenseTileAgents = 2048;
+constexpr uint32_t kSmallIsland = 8;
 
 uint32_t ceil_div(uint32_t a, uint32_t b) { return (a + b - 1) / b; }
 
@@ -521,7 +528,9 @@ int plan_tiles(ga_run* r) {
       if (ws.empty() || ws.back() != ceil_div(W, k)) ws.push_back(ceil_div(W, k));
     for (uint32_t k = 1; k <= H; ++k)
       if (hs.empty() || hs.back() != ceil_div(H, k)) hs.push_back(ceil_div(H, k));
-    const bool one = v.agents <= kOneTileAgents;
+    const bool small = v.log2n < ga::kPairMinLog;
+    const uint32_t weight = small ? kSmallIsland : N;
+    const bool one = small ? v.islands * weight <= kMinTileAgents : v.agents <= kOneTileAgents;
     for (uint32_t tw : ws)
       for (uint32_t th : hs) {
         const TileCand c = tile_cand(v, tw, th);
@@ -531,7 +540,7 @@ int plan_tiles(ga_run* r) {
     auto key = [&](const TileCand& c) {
       const uint64_t tiles = (uint64_t)c.gx * c.gy;
       const bool dense = one ? tiles > 1 : tiles > (uint64_t)cus;
-      const uint64_t agents = std::max<uint64_t>((uint64_t)c.tw * c.th * N,
+      const uint64_t agents = std::max<uint64_t>((uint64_t)c.tw * c.th * weight,
                                                  dense ? kMinDenseTileAgents : kMinTileAgents);
       return std::make_tuple(dense, agents, tiles * (c.tw + c.th), c.tw);
     };

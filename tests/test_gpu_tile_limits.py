@@ -70,3 +70,19 @@ def test_one_agent_islands_at_28_wavefronts_a_cu(policy):
     # one-wavefront tiles, 28 on every CU
     check(dict(width=8 * 28, height=8 * cus, pop=1, sites=32, k=1, policy=policy, seed=83), (8, 8),
           (1, 40))
+
+
+@pytest.mark.parametrize("edge", [
+    dict(width=40, height=40, pop=1, k=1, seed=86), dict(width=5, height=5, pop=1, sites=64, k=1),
+    dict(width=29, height=17, pop=2, sites=64, model=1, k=2, seed=87)],
+    ids=lambda e: f"{e['width']}x{e['height']}x{e['pop']}")
+def test_default_tilings_of_small_islands(edge):
+    cfg = run_config(**edge)
+    run = GARun(cfg)
+    tw, th, n = run.tiles()
+    say(f"default tiling {tw} x {th}, {n} tiles, of {cfg}")
+    assert n > 1 and tw * th <= 16
+    for steps in (1, 8, 31):
+        run.step(steps)
+    assert_same_state(run.read(), oracle_after(cfg, 40), f"tiling {edge}")
+    run.close()

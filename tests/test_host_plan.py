@@ -291,3 +291,19 @@ def test_single_runs_with_and_without_the_librarys_memory(lib, limit):
     for r in (streaming, tiles, lockstep):
         r.close()
     lib.plan_reset((1 << 64) - 1)
+
+
+@pytest.mark.parametrize("kw,most,tiles", [
+    (dict(width=40, height=40, pop=1), 16, None), (dict(width=20, height=10, pop=2), 16, None),
+    (dict(width=45, height=45, pop=1, model=1), 16, None), (dict(width=4, height=4, pop=1), 16, 1),
+    (dict(width=16, height=16, pop=8), 256, 1), (dict(width=22, height=22, pop=4), 484, 1),
+    (dict(width=8, height=8, pop=32), 64, 1), (dict(width=37, height=23, pop=16), 12, None)])
+def test_default_tiles_keep_a_wavefront_to_one_pass(lib, kw, most, tiles):
+    r = Run(lib, **kw)
+    w, h, n = (ctypes.c_uint32() for _ in range(3))
+    assert lib.ga_get_tiles(r.h, ctypes.byref(w), ctypes.byref(h), ctypes.byref(n)) == 0
+    assert 1 <= w.value * h.value <= most and n.value <= 256
+    assert n.value == tiles if tiles else n.value > 1
+    r.step(9)
+    assert r.ran() == 9
+    r.close()
