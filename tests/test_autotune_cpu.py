@@ -83,6 +83,17 @@ def test_a_faster_chunk_is_kept_and_the_rest_stay_on_the_rule(tuner):
     assert pool.settings == {(3, 2): 0, (5, 1): 8} and pool.launch == (0, 4)
 
 
+def test_a_card_that_warms_up_makes_nothing_win(tuner):
+    clock = [1.0]
+
+    def seconds(used, wpg):
+        clock[0] *= 0.97             # every timing 3% faster than the one before
+        return clock[0] * (1.0 if used == FakeBatch.rule else 1.02)
+    batch, chosen = tuner(seconds)
+    assert set(chosen["by_rule"]) == set(CLASSES)
+    assert {k: batch.class_launch(*k)[0] for k in CLASSES} == FakeBatch.rule
+
+
 def test_group_size_is_searched_where_single_generations_run(tuner):
     cfgs = [run_config(width=9, height=9, pop=2)] + CFGS
     FakeBatch.rule[(1, 2)] = FakeBatch.most[(1, 2)] = 64
