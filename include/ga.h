@@ -299,9 +299,10 @@ int ga_set_launch(ga_run* run, uint32_t islands_per_wave, uint32_t waves_per_gro
  * 2,048 agents, else the smallest tiles of 128 agents or more of which there is
  * at most one per CU, where such fit, else the smallest of 2,048 or more, islands
  * of one or two agents counting as 8 and making one tile up to 16 of them, whose
- * workgroups all fit the GPU at once; then the shortest edges in all). GA_EINVAL for an asynchronous run, for one side
- * given without the other, or if the tiles do not fit (LDS of a CU, or more
- * workgroups than the GPU holds at once); the run then keeps its tiling.
+ * workgroups all fit the GPU at once; then the shortest edges in all).
+ * GA_EINVAL for an asynchronous run, for one side given without the other, or if
+ * the tiles do not fit (LDS of a CU, or more workgroups than the GPU holds at
+ * once); the run then keeps its tiling.
  * Results do not depend on the tile shape. */
 int ga_set_tiles(ga_run* run, uint32_t tile_w, uint32_t tile_h);
 

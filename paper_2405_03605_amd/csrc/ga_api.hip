@@ -462,14 +462,13 @@ uint32_t waves_for(const ga_run* r, uint32_t ipw) {
 constexpr size_t kMaxGroupLds = 160 * 1024;
 
 // The default tiling. A run of up to kOneTileAgents is one tile, which waits for
-// nobody (8 x 8 x 32: 1.69 us per generation; four tiles to sixteen would be at
-// 1.6). Larger ones take the smallest tiles of kMinTileAgents or more that leave
-// at most one per CU: the exchange costs about 0.5 us a generation however many
-// tiles there are, a wavefront's pass more than that (16 x 16 x 32 in tiles of 64,
-// 128, 256, 512, 1024, 2048 and 4096 agents: 1.60 1.56 1.65 1.73 2.07 2.32 2.84 us;
-// 37 x 23 x 16: 1.65 1.66 1.64 1.73 2.07 2.32 2.88), until CUs have two tiles
-// (64 x 64 x 32 in 256 tiles: 1.78, in 512: 1.84, in 2048: 2.95; 100 x 100 x 32
-// in 169: 2.35, in 1250: 2.58). Without such a tiling kMinDenseTileAgents holds.
+// nobody (8 x 8 x 32: 1.69 us per generation; 4, 8 and 16 tiles: 1.40 1.31 1.28).
+// Larger ones take the smallest tiles of kMinTileAgents or more that leave at most
+// one per CU: the exchange costs little however many tiles there are, a wavefront's
+// pass more than that (16 x 16 x 32 in tiles of 64, 128, 256, 512, 1024, 2048 and
+// 4096 agents: 1.29 1.29 1.32 1.42 1.64 1.94 2.52 us; 37 x 23 x 16: 1.33 1.37 1.42
+// 1.50 1.74 2.22 3.16), until CUs have two tiles (64 x 64 x 32 in 256 tiles: 1.45, in
+// 512: 1.47, in 2048: 1.76; 100 x 100 x 32 in 169: 1.99, in 1250: 2.86). Without such a tiling kMinDenseTileAgents holds.
 // Islands of one or two agents count as kSmallIsland of them: a wavefront's pass
 // covers 16 islands, so 64 agents of those take four passes or two in turn (40 x
 // 40 x 1 in tiles of 1,600, 800, 400, 128, 64, 32 and 16 islands: 6.20 3.02 2.67 2.43
@@ -817,9 +816,10 @@ namespace {
 
 // What a run that may be stepped by itself has beside the caller's memory: the
 // candidates of the streaming form, and the exchange area of the LDS-resident one
-// where the population could fit the GPU's LDS, or an asynchronous run's outbox. One small allocation of the
-// library's own; without it (no memory left) the forms run one generation per
-// launch. Made here, not on the first step, so that a step can be captured.
+// where the population could fit the GPU's LDS, or an asynchronous run's outbox.
+// One block of the library's own; without it (no memory left) the forms run one
+// generation per launch. Taken here, not on the first step, so that a step can be
+// captured.
 void alloc_own(ga_run* r) {
   ga::RunView& v = r->view;
   int device = 0, cus = 0;

@@ -71,7 +71,8 @@ struct RunView {
   unsigned long long* exchange;
   // streaming form, two generations a launch: the candidates, island i's of
   // generation t in cand[((t >> 1 & 1) * island_stride + i) * ob_stride + k], k as
-  // in an outbox entry (no header); NULL without them
+  // in an outbox entry, the island's draw of t packed in the header word; NULL
+  // without them
   uint32_t* cand;
   // what a streaming launch does (kSpan*)
   uint32_t span;

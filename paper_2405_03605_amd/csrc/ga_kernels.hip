@@ -21,9 +21,11 @@
 // other wavefront reads them. Population and outbox planes are padded past the
 // last island, so iterations never need a tail predicate.
 //
-// Runs stepped by four generations and more take two per launch instead
-// (ga_pair.hpp); this kernel has what is left over, islands of fewer than four
-// members, batches and the asynchronous schedule.
+// Runs and batches stepped by four generations and more take two per launch
+// instead (ga_pair.hpp), asynchronous ones at the default pacing from 48 on between
+// their first and last; one generation per launch is for what is left over, islands
+// of fewer than four members (and batches with such a member), and runs without
+// memory for candidates.
 #include "ga_pair.hpp"
 
 namespace ga {

@@ -22,11 +22,11 @@
 // single-generation launch expects; the host runs them in fours.
 //
 // Bound: the matrix cores have nothing to do here; HBM (26 bytes per agent a
-// launch, 6.1 of the 7.2 TB/s an in-place update reaches) and VALU (77
+// launch, 5.9 of the 7.2 TB/s an in-place update reaches) and VALU (77
 // instructions per 64 children, 59 of them in the loop; 0.89 of the issue slots)
-// together. 1024 x 512 x 32, k = 2: 36 us per generation (72 a launch) against
+// together. 1024 x 512 x 32, k = 2: 37 us per generation (74 a launch) against
 // 62 for the single-generation kernel; 300 x 200 x 64 trap-4 on the hybrid
-// surface, k = 3: 18.6 against 34.2; it is ahead at every
+// surface, k = 3: 18.7 against 34.2; it is ahead at every
 // grid and island size from four members up (16 x 16 x 32: 1.8 against 3.2,
 // 4096 x 1024 x 32: 326 against 645). What made it so: arrivals and draws kept
 // in registers, four lanes an island, so that LDS holds 24 wavefronts a CU

@@ -52,8 +52,8 @@
 // that gave up is counted, which the host reports as an error when the state
 // is read.
 //
-// Bound: VALU issue (256 x 256 x 32 on 16 x 16 tiles: 2,349 vector instructions
-// per SIMD and generation in 10,690 cycles), so what is not Philox is kept
+// Bound: VALU issue (256 x 256 x 32 on 32 x 8 tiles: 2,385 vector instructions
+// per SIMD and generation in 10,756 cycles), so what is not Philox is kept
 // short: parents are gathered from planes by address (no permutes, no arrival
 // test, no record read and write: 4.3 cycles a gather against 7.3 a permute),
 // constants sit in vector registers (see and_or in ga_device.hpp), and a
@@ -63,8 +63,9 @@
 // SIMD at one instruction in nine cycles. Measured, microseconds per
 // generation, against the form before (16-byte records, one thread per island
 // in a pass between two workgroup barriers, per-tile progress words):
-// 256 x 256 x 32 5.9 to 4.45 (5.2 with the hardware's priority), 100 x 100 x 32
-// treatments 5.3 to 2.8, 37 x 23 x 16 k = 5 3.8 to 2.7, 8 x 8 x 32 2.6 to 1.7.
+// 256 x 256 x 32 6.0 to 4.4 (5.2 with the hardware's priority; 4.6 where waiting
+// wavefronts retry without a pause), 100 x 100 x 32 treatments 5.4 to 2.8, 37 x 23 x
+// 16 k = 5 3.9 to 1.6 (2.2 on tiles of 2,048 agents), 8 x 8 x 32 2.6 to 1.7.
 #include <algorithm>
 
 #include "ga_device.hpp"
@@ -339,8 +340,8 @@ void tile_kernel(RunView v, uint32_t n_gens) {
   // one address unit busy, and a wavefront whose stores some of them wait for gets
   // no turn until their tries run out (islands of one agent in 20 one-wavefront
   // tiles a CU: single passes held up for 30 to 52 ms, the run invalid). 24 such
-  // tiles a CU: 13.5 us per generation, 18.8 asleep for half as long, 43 and more
-  // for a quarter or after 16 tries; 12 two-wavefront tiles of 32-agent islands 3.67
+  // tiles a CU: 13.5 us per generation, 18.8 asleep half as long, 34 a quarter, 68
+  // with the first 16 tries at once; 24 tiles a CU of two 32-agent islands 3.67
   // against 3.55.
   uint32_t gave_up = 0u;
   auto wait_for = [&](bool on, uint32_t from, uint32_t stamp, uint32_t pair) {
