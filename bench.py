@@ -256,7 +256,9 @@ def bench_batched(gens: int, torch, tune: bool = True):
 
 def shape_names(chosen: dict) -> dict:
     """autotune_batch's choice with readable class names."""
-    out = {"waves_per_group": chosen["waves_per_group"]}
+    # (launches of two generations go in groups of one wavefront whatever is set)
+    single = any(isinstance(k, tuple) and k[0] < 2 for k in chosen)
+    out = {"waves_per_group": chosen["waves_per_group"]} if single else {}
     by_rule = chosen.get("by_rule", ())
     out.update({f"N={1 << k[0]},words={k[1]}":
                 {"islands_per_wave": v, "chosen": "rule" if k in by_rule else "timed"}

@@ -52,8 +52,8 @@
 // that gave up is counted, which the host reports as an error when the state
 // is read.
 //
-// Bound: VALU issue (256 x 256 x 32 on 32 x 8 tiles: 2,385 vector instructions
-// per SIMD and generation in 10,756 cycles), so what is not Philox is kept
+// Bound: VALU issue (256 x 256 x 32 on 32 x 8 tiles: 2,390 vector instructions
+// per SIMD and generation in 10,800 cycles), so what is not Philox is kept
 // short: parents are gathered from planes by address (no permutes, no arrival
 // test, no record read and write: 4.3 cycles a gather against 7.3 a permute),
 // constants sit in vector registers (see and_or in ga_device.hpp), and a
