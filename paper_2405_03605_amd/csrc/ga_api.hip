@@ -493,12 +493,28 @@ TileCand tile_cand(const ga::RunView& v, uint32_t tw, uint32_t th) {
   return c;
 }
 
-// Whether every tile's workgroup of candidate c can be resident at once:
-// first a bound from LDS and threads per CU alone, then the occupancy query.
+// Whether every tile's workgroup of candidate c can be resident at once: first a
+// bound from LDS, wavefronts and threads per CU alone, then the occupancy query,
+// which promises more than a CU holds in two respects.
+//  LDS: a CU gives it out in 1,280 bytes. Of the 23 8 x 8 tiles of one-agent
+//   islands with two surface words that 160 KiB hold at their 6,792 bytes each, 21
+//   are resident; of 12 16 x 8 tiles (13,000 bytes) 11, of 6 strings' 16 x 16 tiles
+//   (26,888 bytes) 5.
+//  Wavefronts: a kernel that uses more than 96 scalar registers runs at six a SIMD
+//   (of 800, 112 and the 16 that every wavefront has besides), where its 72 vector
+//   registers would let seven. Only the kernel of one-agent islands without a
+//   string and with one surface word uses fewer and holds 28 a CU; strings' tiles
+//   (2 x 1, 2 x 2 and 1 x 1 of 32 and 64 agents) are resident at 24, not at 25 or 26.
+constexpr size_t kLdsGranule = 1280;
+constexpr uint32_t kTileWaves = 24, kTileWavesOneAgent = 28;
+
 int tile_fits(const ga::RunView& v, const TileCand& c, uint32_t cus, bool* fits) {
   *fits = false;
   if (c.lds > kMaxGroupLds || (size_t)c.gx * c.gy > kMaxTiles) return GA_OK;
-  const uint64_t bound = std::min<uint64_t>(kMaxGroupLds / c.lds, 2048u / c.threads);
+  const size_t lds = (c.lds + kLdsGranule - 1) / kLdsGranule * kLdsGranule;
+  const bool one = v.log2n == 0 && v.words == 1 && !ga::model_has_string_host(v.model);
+  const uint32_t waves = one ? kTileWavesOneAgent : kTileWaves;
+  const uint64_t bound = std::min<uint64_t>(kMaxGroupLds / lds, waves / (c.threads / 64u));
   if ((uint64_t)c.gx * c.gy > bound * cus) return GA_OK;
   int groups = 0;
   GA_HIP(ga::tile_occupancy(v, c.threads, c.lds, &groups), "occupancy query");

@@ -1,10 +1,11 @@
 """The LDS-resident form at the edges of what it accepts, bit for bit against the
 oracle: tiles within 400 bytes of a CU's LDS, with islands of one, two and four
-agents, and tiles of a few such islands, whose read-ahead ends past their outbox."""
+agents, and tiles of a few such islands, whose read-ahead ends past their outbox;
+as many tiles as are resident at once, and the refusal of more."""
 import pytest
 
 from gpu_helpers import assert_same_state, oracle_after, say
-from paper_2405_03605_amd import FORM_RESIDENT, GARun
+from paper_2405_03605_amd import FORM_RESIDENT, GAError, GARun
 from paper_2405_03605_amd.workloads import run_config
 
 pytestmark = pytest.mark.gpu
@@ -70,6 +71,29 @@ def test_one_agent_islands_at_28_wavefronts_a_cu(policy):
     # one-wavefront tiles, 28 on every CU
     check(dict(width=8 * 28, height=8 * cus, pop=1, sites=32, k=1, policy=policy, seed=83), (8, 8),
           (1, 40))
+
+
+@pytest.mark.parametrize("edge,tile,most", [
+    (dict(pop=1, sites=64, k=1), (8, 8), 21),
+    (dict(pop=1, sites=64, k=1), (16, 8), 11),
+    (dict(pop=1, sites=64, k=1, model=2, policy=1), (16, 16), 5),
+    (dict(pop=1, sites=32, k=1), (8, 8), 28),
+    (dict(pop=32, sites=32, k=2, model=1), (2, 1), 24),
+    (dict(pop=32, sites=32, k=2, model=1), (2, 2), 12),
+    (dict(pop=64, sites=32, k=2, model=2), (1, 1), 24)],
+    ids=lambda e: f"N{e['pop']}S{e['sites']}m{e.get('model', 0)}" if isinstance(e, dict) else None)
+def test_most_tiles_a_cu(edge, tile, most):
+    # by the LDS each takes (in pieces of 1,280 bytes), or by its wavefronts
+    import torch
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    size = dict(height=tile[1] * cus // 4)
+    check(dict(edge, width=tile[0] * 4 * most, seed=88, **size), tile, (1, 20))
+    run = GARun(run_config(**edge, width=tile[0] * 4 * (most + 1), seed=89, **size))
+    run.set_launch(form=FORM_RESIDENT)
+    with pytest.raises(GAError):
+        run.set_tiles(*tile)
+        run.tiles()
+    run.close()
 
 
 @pytest.mark.parametrize("edge", [
