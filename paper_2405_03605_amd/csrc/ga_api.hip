@@ -458,8 +458,15 @@ uint32_t waves_for(const ga_run* r, uint32_t ipw) {
   return (r->view.islands + ipw - 1) / ipw;
 }
 
-// LDS of one CU (gfx950), the most a workgroup can take.
-constexpr size_t kMaxGroupLds = 160 * 1024;
+// LDS of one CU (gfx950), the most a workgroup can take, and the pieces it is given
+// out in, which the occupancy query does not count in.
+constexpr size_t kMaxGroupLds = 160 * 1024, kLdsGranule = 1280;
+
+// Workgroups of `lds` bytes that a CU's LDS holds at once.
+uint32_t groups_by_lds(size_t lds) {
+  const size_t given = std::max<size_t>(1, (lds + kLdsGranule - 1) / kLdsGranule) * kLdsGranule;
+  return (uint32_t)(kMaxGroupLds / given);
+}
 
 // The default tiling. A run of up to kOneTileAgents is one tile, which waits for
 // nobody (8 x 8 x 32: 1.69 us per generation; 4, 8 and 16 tiles: 1.40 1.31 1.28).
@@ -505,16 +512,14 @@ TileCand tile_cand(const ga::RunView& v, uint32_t tw, uint32_t th) {
 //   registers would let seven. Only the kernel of one-agent islands without a
 //   string and with one surface word uses fewer and holds 28 a CU; strings' tiles
 //   (2 x 1, 2 x 2 and 1 x 1 of 32 and 64 agents) are resident at 24, not at 25 or 26.
-constexpr size_t kLdsGranule = 1280;
 constexpr uint32_t kTileWaves = 24, kTileWavesOneAgent = 28;
 
 int tile_fits(const ga::RunView& v, const TileCand& c, uint32_t cus, bool* fits) {
   *fits = false;
   if (c.lds > kMaxGroupLds || (size_t)c.gx * c.gy > kMaxTiles) return GA_OK;
-  const size_t lds = (c.lds + kLdsGranule - 1) / kLdsGranule * kLdsGranule;
   const bool one = v.log2n == 0 && v.words == 1 && !ga::model_has_string_host(v.model);
   const uint32_t waves = one ? kTileWavesOneAgent : kTileWaves;
-  const uint64_t bound = std::min<uint64_t>(kMaxGroupLds / lds, waves / (c.threads / 64u));
+  const uint64_t bound = std::min(groups_by_lds(c.lds), waves / (c.threads / 64u));
   if ((uint64_t)c.gx * c.gy > bound * cus) return GA_OK;
   int groups = 0;
   GA_HIP(ga::tile_occupancy(v, c.threads, c.lds, &groups), "occupancy query");
@@ -748,6 +753,19 @@ int step_lockstep(ga_run* r, uint64_t n) {
   return one();
 }
 
+// Wavefronts of the asynchronous kernels that the GPU holds at once, which is less
+// than the occupancy query says for groups whose LDS is rounded up by much: 25 a CU,
+// not 31, at one wavefront a group and 64 islands each (32 with a string).
+int async_waves(const ga_run* r, const ga::RunView& v, bool lockstep, uint32_t* waves) {
+  int device = 0, cus = 0;
+  GA_HIP(hipGetDevice(&device), "get device");
+  GA_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device), "CU count");
+  GA_HIP(ga::async_capacity(v, r->wpg, lockstep, waves), "occupancy query");
+  const uint32_t groups = groups_by_lds(ga::lds_bytes(v.ipw, r->wpg, v.model));
+  *waves = std::min(*waves, groups * r->wpg * (uint32_t)cus);
+  return GA_OK;
+}
+
 // Asynchronous schedule: one persistent launch per slice of generations, the
 // chunks spread over as many wavefronts as the GPU holds at once (or over the
 // caller's cap), each wavefront owning consecutive chunks.
@@ -760,7 +778,8 @@ int step_async(ga_run* r, uint64_t n) {
   // no lead and no skew: the lockstep exchange
   const bool lockstep = r->async_lead == 0u && r->async_skew == 0u;
   uint32_t cap = 0;
-  GA_HIP(ga::async_capacity(v, r->wpg, lockstep, &cap), "occupancy query");
+  int rc = async_waves(r, v, lockstep, &cap);
+  if (rc != GA_OK) return rc;
   // With the default chunk size (and no skew, whose one-wavefront
   // interleavings name their chunks): while each resident wavefront would run
   // more than two chunks in turn (waiting out each one's exchange), take
@@ -771,7 +790,8 @@ int step_async(ga_run* r, uint64_t n) {
   while (r->async_skew == 0u && !r->ipw_set && waves_for(r, v.ipw) > 2u * cap &&
          v.ipw * 2u <= 64u && ga::lds_bytes(v.ipw * 2u, r->wpg, v.model) <= kMaxGroupLds) {
     v.ipw *= 2u;
-    GA_HIP(ga::async_capacity(v, r->wpg, lockstep, &cap), "occupancy query");
+    rc = async_waves(r, v, lockstep, &cap);
+    if (rc != GA_OK) return rc;
   }
   const uint32_t chunks = waves_for(r, v.ipw);
   uint32_t waves = std::max(1u, std::min(chunks, cap));

@@ -175,17 +175,26 @@ uint32_t tile_threads(uint32_t w, uint32_t h, uint32_t l) {
   return 64u * std::min(16u, ((w * h << l) + 63u) / 64u);
 }
 hipError_t tile_occupancy(const RunView&, uint32_t threads, size_t, int* g) { *g = (int)(1024u / threads); return hipSuccess; }
-hipError_t launch_async(const RunView& v, uint64_t n, uint32_t, uint32_t, uint32_t, uint32_t, uint32_t, hipStream_t s) {
+// What a CU holds at once of groups of `wpg` wavefronts: 32 wavefronts, and LDS,
+// given out in pieces of `piece` bytes.
+uint32_t resident(const RunView& v, uint32_t wpg, size_t piece) {
+  const size_t lds = (lds_bytes(v.ipw, wpg, v.model) + piece - 1) / piece * piece;
+  return (uint32_t)std::min<size_t>(32u / wpg, (160u << 10) / lds) * 256u;
+}
+hipError_t launch_async(const RunView& v, uint64_t n, uint32_t waves, uint32_t, uint32_t wpg, uint32_t, uint32_t, hipStream_t s) {
+  if ((waves + wpg - 1) / wpg > resident(v, wpg, 1280)) stop("more groups than are resident");
   return run(s, [=] { breed(v, 0, v.islands, *v.gen, (uint32_t)n); });
 }
-hipError_t launch_lockstep(const RunView& v, uint64_t gen, uint64_t n, uint32_t, uint32_t, uint32_t, hipStream_t s) {
+hipError_t launch_lockstep(const RunView& v, uint64_t gen, uint64_t n, uint32_t waves, uint32_t, uint32_t wpg, hipStream_t s) {
+  if ((waves + wpg - 1) / wpg > resident(v, wpg, 1280)) stop("more groups than are resident");
   return run(s, [=] {
     if (gen != *v.gen) stop("lockstep launch at another generation");
     persistent += 1;
     breed(v, 0, v.islands, gen, (uint32_t)n);
   });
 }
-hipError_t async_capacity(const RunView&, uint32_t, bool, uint32_t* w) { *w = 4096; return hipSuccess; }
+// as the occupancy query, which does not know the pieces
+hipError_t async_capacity(const RunView& v, uint32_t wpg, bool, uint32_t* w) { *w = resident(v, wpg, 1) * wpg; return hipSuccess; }
 hipError_t launch_advance(unsigned long long* g, uint64_t n, hipStream_t s) { return run(s, [=] { *g += n; }); }
 hipError_t launch_init(const RunView&, hipStream_t) { return hipSuccess; }
 bool model_has_string_host(uint32_t id) { return id != 0; }

@@ -63,3 +63,25 @@ def test_persistent_launches_at_full_size(kw, gens, cap):
     run.close()
     for key in ("f", "T", "D"):
         assert np.array_equal(got[key].view(np.uint32), want[key].view(np.uint32)), key
+
+
+@pytest.mark.parametrize("pop,ipw,wpg,width,height,model", [
+    (4, 32, 1, 512, 448, 1), (1, 64, 1, 1024, 448, 0), (1, 64, 2, 1024, 480, 0)])
+def test_groups_by_the_lds_they_are_given(pop, ipw, wpg, width, height, model):
+    # 28 and 30 wavefronts a CU by the LDS asked for, 25 and 28 by the LDS given out
+    kw = dict(width=width, height=height, pop=pop, sites=32, k=2, model=model)
+    say(f"persistent lockstep at {ipw} x {wpg}, {kw}")
+    sync = GARun(run_config(**kw))
+    sync.step(60)
+    want = sync.read(outbox=False)
+    sync.close()
+    run = GARun(run_config(schedule=SCHEDULE_ASYNC, **kw))
+    run.set_launch(ipw, wpg)
+    run.set_async(UNCAPPED)
+    run.step(60)
+    got = run.read()
+    assert run.async_waits() == 0
+    assert run.async_taken() == width * height * 59
+    run.close()
+    for key in ("f", "T", "D") + (("P",) if model else ()):
+        assert np.array_equal(got[key].view(np.uint32), want[key].view(np.uint32)), key

@@ -307,3 +307,18 @@ def test_default_tiles_keep_a_wavefront_to_one_pass(lib, kw, most, tiles):
     r.step(9)
     assert r.ran() == 9
     r.close()
+
+
+@pytest.mark.parametrize("ipw,wpg,kw", [
+    (64, 1, dict(width=1024, height=448, pop=1)), (32, 1, dict(width=512, height=448, pop=2, model=1)),
+    (64, 2, dict(width=1024, height=480, pop=1)), (48, 2, dict(width=768, height=352, pop=4, model=2)),
+    (32, 4, dict(width=512, height=448, pop=2, model=1)), (16, 4, dict(width=512, height=256, pop=4))])
+@pytest.mark.parametrize("pacing", [(0, 0, 0), (1 << 20, 0, 0), (0, 2, 0)])
+def test_asynchronous_launches_are_resident_at_once(lib, ipw, wpg, kw, pacing):
+    # the stand-in launches count their groups' LDS as a CU gives it out
+    r = Run(lib, schedule=1, **kw)
+    assert lib.ga_set_launch(r.h, ipw, wpg, 0) == 0
+    assert lib.ga_set_async(r.h, *pacing) == 0
+    r.step(7)
+    assert r.ran() == 7
+    r.close()
